@@ -372,6 +372,10 @@ bool rank_vars(Ctx &c);
 // Writes the n records at src (device) into dst (device) ordered by (clause id,
 // word); synchronises the stream.
 void sort_records(Ctx &c, gss_report *src, uint64_t n, gss_report *dst);  // src is overwritten
+// The same order straight from the report segments, by ranking (id, word) cells:
+// workspace bytes (0: use sort_records) and the queued launches.
+uint64_t rank_bytes(const Ctx &c);
+void rank_records(Ctx &c, char *ws, gss_report *dst, uint64_t limit);
 void launch_scan_u32(Ctx &c, uint32_t *x, uint64_t m);  // in place, exclusive, on c.stream
 uint32_t *deferred_flag(Ctx &c);
 uint32_t read_deferred(Ctx &c);

@@ -1,6 +1,17 @@
-// Ordered reports (GSS_TEST_SORTED): the kept records of a test, sorted by
-// (clause id, word) with a least-significant-digit radix sort written for this
-// library.  The key packs clause id and word ((id << word_bits) | word); each
+// Ordered reports (GSS_TEST_SORTED): the kept records of a test, ordered by
+// (clause id, word).  Two ways, one result:
+//
+// Ranked (rank_records): a test has at most one record per (clause id, word), so a
+// record's place is the number of records at smaller (id, word) cells.  One pass
+// over the report segments marks the cells (a byte store each: no two records
+// share one, so no atomics), one over the cells packs them into words of 64 bits
+// with their running counts, and one more over the segments stores each record at
+// its place.  The records are read twice and written once, straight from the
+// segments.
+//
+// Radix (sort_records), where the cells would be many times the records (a large
+// store with few hits) or do not fit the memory budget: a least-significant-digit
+// radix sort written for this library.  The key packs clause id and word ((id << word_bits) | word); each
 // pass orders the 16-byte records stably by one 8-bit digit of it:
 //
 //   1. per workgroup tile of 4096 records, the count of each digit (LDS);
@@ -60,6 +71,53 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_tile_counts(const gss_rep
         atomicAdd(&h[(record_key(r[i], word_bits) >> shift) & 0xFF], 1u);
     __syncthreads();
     hist[(uint64_t)threadIdx.x * n_tiles + blockIdx.x] = h[threadIdx.x];
+}
+
+// Scan of many counts in three launches: sums of chunks of 4096, their scan by one
+// workgroup, the chunks again from their bases.  One workgroup alone read 610
+// counts a thread, one line each, for the 625 K counts of 10 M records: 1.2 ms for
+// each of the four passes' scans.
+constexpr uint32_t kScanChunk = 4096;
+
+__global__ __launch_bounds__(256) void k_scan_sums(const uint32_t *x, uint64_t m, uint32_t *sums) {
+    __shared__ uint32_t part[4];
+    const uint64_t lo = (uint64_t)blockIdx.x * kScanChunk + threadIdx.x;
+    uint32_t v = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kScanChunk; k += 256) v += lo + k < m ? x[lo + k] : 0u;
+    for (uint32_t off = 32; off; off >>= 1) v += __shfl_xor(v, off);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x / 64] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) sums[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
+}
+
+// x becomes its exclusive scan; sums: the chunks' bases.  Round r takes 256 counts.
+__global__ __launch_bounds__(256) void k_scan_apply(uint32_t *x, uint64_t m, const uint32_t *sums) {
+    __shared__ uint32_t wave_sum[2][4];
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint64_t lo = (uint64_t)blockIdx.x * kScanChunk + threadIdx.x;
+    uint32_t v[kScanChunk / 256];
+#pragma unroll
+    for (uint32_t k = 0; k < kScanChunk / 256; ++k) v[k] = lo + 256 * k < m ? x[lo + 256 * k] : 0u;
+    uint32_t run = sums[blockIdx.x];
+#pragma unroll
+    for (uint32_t k = 0; k < kScanChunk / 256; ++k) {
+        uint32_t s = v[k];
+#pragma unroll
+        for (uint32_t d = 1; d < 64; d <<= 1) {
+            const uint32_t y = __shfl_up(s, d);
+            if (lane >= d) s += y;
+        }
+        if (lane == 63) wave_sum[k & 1][wave] = s;
+        __syncthreads();  // the other half of wave_sum is rewritten only behind the next round's barrier
+        uint32_t before = run;
+#pragma unroll
+        for (uint32_t w = 0; w < 4; ++w) {
+            before += w < wave ? wave_sum[k & 1][w] : 0u;
+            run += wave_sum[k & 1][w];
+        }
+        if (lo + 256 * k < m) x[lo + 256 * k] = before + s - v[k];
+    }
 }
 
 // In-place exclusive scan of m counts by one workgroup of 1024 threads, each
@@ -132,6 +190,90 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(const gss_report 
     }
 }
 
+// ---- ranked order ------------------------------------------------------------
+
+constexpr uint32_t kRankBlock = 1u << 16;  // cells per workgroup of the packing kernel (1024 words of 64)
+
+// cells[id << w_log2 | word] = 1 for every kept record; one workgroup per segment.
+// Bound by the segments' reads (8 of each record's 16 bytes are used, but whole
+// lines come in).  Segments grown after a test that lost records hold none yet:
+// what is read there may be no cell, and is left out (here and below).
+__global__ __launch_bounds__(256) void k_rank_mark(const gss_report *reports, const uint32_t *counts, uint32_t seg_cap,
+                                                   uint32_t n_segments, uint32_t w_log2, uint32_t n_cells,
+                                                   uint8_t *cells) {
+    for (uint32_t s = blockIdx.x; s < n_segments; s += gridDim.x) {
+        const uint32_t n = min(counts[s], seg_cap);
+        const gss_report *seg = reports + (uint64_t)s * seg_cap;
+        for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
+            const uint64_t cell = ((uint64_t)seg[i].clause_id << w_log2) + seg[i].word;
+            if (cell < n_cells) cells[cell] = 1;
+        }
+    }
+}
+
+// Packs 64 cells a lane into (bits, bits, cells marked before them in the
+// workgroup's 65536, 0), and the workgroup's total.  Four rounds of 256 words; the
+// running count crosses rounds in a register every lane holds.
+__global__ __launch_bounds__(256) void k_rank_pack(const uint4 *cells, uint32_t n_words, uint4 *packed,
+                                                   uint32_t *totals) {
+    __shared__ uint32_t wave_sum[2][4];
+    const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    uint32_t run = 0;
+#pragma unroll
+    for (uint32_t r = 0; r < kRankBlock / 64 / 256; ++r) {
+        const uint32_t w = blockIdx.x * (kRankBlock / 64) + 256 * r + t;
+        uint32_t bits[2] = {0, 0};
+        if (w < n_words) {
+#pragma unroll
+            for (uint32_t q = 0; q < 4; ++q) {
+                const uint4 c = cells[(uint64_t)w * 4 + q];
+                const uint32_t u[4] = {c.x, c.y, c.z, c.w};
+                // four cells (bytes 0 or 1) to four bits: byte i lands on bit 28 + i of the product
+#pragma unroll
+                for (uint32_t k = 0; k < 4; ++k) bits[q / 2] |= ((u[k] * 0x10204080u) >> 28) << (16 * (q % 2) + 4 * k);
+            }
+        }
+        const uint32_t mine = __builtin_popcount(bits[0]) + __builtin_popcount(bits[1]);
+        uint32_t x = mine;
+#pragma unroll
+        for (uint32_t d = 1; d < 64; d <<= 1) {
+            const uint32_t y = __shfl_up(x, d);
+            if (lane >= d) x += y;
+        }
+        if (lane == 63) wave_sum[r & 1][wave] = x;
+        __syncthreads();  // the other half of wave_sum is rewritten only behind the next round's barrier
+        uint32_t before = run;
+#pragma unroll
+        for (uint32_t v = 0; v < 4; ++v) {
+            before += v < wave ? wave_sum[r & 1][v] : 0u;
+            run += wave_sum[r & 1][v];
+        }
+        if (w < n_words) packed[w] = make_uint4(bits[0], bits[1], before + x - mine, 0u);
+    }
+    if (t == 0) totals[blockIdx.x] = run;
+}
+
+// Stores every kept record at its place; places at or beyond `limit` are left out.
+__global__ __launch_bounds__(256) void k_rank_place(const gss_report *reports, const uint32_t *counts, uint32_t seg_cap,
+                                                    uint32_t n_segments, uint32_t w_log2, uint32_t n_cells,
+                                                    const uint4 *packed, const uint32_t *base, uint64_t limit,
+                                                    gss_report *out) {
+    for (uint32_t s = blockIdx.x; s < n_segments; s += gridDim.x) {
+        const uint32_t n = min(counts[s], seg_cap);
+        const uint4 *seg = reinterpret_cast<const uint4 *>(reports) + (uint64_t)s * seg_cap;
+        for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
+            const uint4 rec = seg[i];
+            const uint64_t at = ((uint64_t)rec.x << w_log2) + rec.y;
+            if (at >= n_cells) continue;
+            const uint32_t cell = (uint32_t)at;
+            const uint4 p = packed[cell >> 6];
+            const uint64_t below = (((uint64_t)p.y << 32) | p.x) & ((1ull << (cell & 63)) - 1);
+            const uint64_t pos = (uint64_t)base[cell / kRankBlock] + p.z + __builtin_popcountll(below);
+            if (pos < limit) reinterpret_cast<uint4 *>(out)[pos] = rec;
+        }
+    }
+}
+
 unsigned grid_of(uint64_t n) { return (unsigned)std::max<uint64_t>(1, std::min<uint64_t>((n + 255) / 256, 16384)); }
 
 }  // namespace
@@ -139,6 +281,49 @@ unsigned grid_of(uint64_t n) { return (unsigned)std::max<uint64_t>(1, std::min<u
 void launch_scan_u32(Ctx &c, uint32_t *x, uint64_t m) {
     if (m == 0) return;
     hipLaunchKernelGGL(k_sort_scan, dim3(1), dim3(1024), 0, c.stream, x, m);
+    GSS_HIP(hipGetLastError());
+}
+
+// Cells of the ranked order: issued ids x words, a power of two of words per id.
+static uint64_t rank_cells(const Ctx &c, uint32_t &w_log2) {
+    w_log2 = 0;
+    while ((1u << w_log2) < c.W) ++w_log2;
+    return ((uint64_t)c.id_loc.size() << w_log2) + 64;
+}
+
+// Bytes of the ranked order's workspace for the last test's records, or 0 where the
+// radix sort is used.  Ranking costs its cells (cleared and read once: 82 us for 96 M
+// cells with 815 K records, 53 us for 64 M with 103 K) and about 25 ns per thousand
+// records; the radix sort costs 158 us for 43 K records, 238 us for 815 K.  So ranking
+// wins up to about 160 M cells plus 128 a record.  The kernels index cells by 32 bits.
+uint64_t rank_bytes(const Ctx &c) {
+    uint32_t w_log2;
+    const uint64_t cells = rank_cells(c, w_log2);
+    if (cells >= (1ull << 32) || cells > (160ull << 20) + 128 * c.n_kept) return 0;
+    const uint64_t words = (cells + 63) / 64, blocks = (cells + kRankBlock - 1) / kRankBlock;
+    return words * 64 + words * 16 + (blocks * 4 + 255) / 256 * 256;
+}
+
+// Queues the ranked order of the last test's kept records, the first `limit` of it,
+// into dst (device); ws: rank_bytes of device memory, 256-byte aligned.
+void rank_records(Ctx &c, char *ws, gss_report *dst, uint64_t limit) {
+    uint32_t w_log2;
+    const uint64_t cells = rank_cells(c, w_log2);
+    const uint64_t words = (cells + 63) / 64, blocks = (cells + kRankBlock - 1) / kRankBlock;
+    uint8_t *flags = (uint8_t *)ws;
+    uint4 *packed = (uint4 *)(ws + words * 64);
+    uint32_t *totals = (uint32_t *)(ws + words * 64 + words * 16);
+    launch_fill_u64(c, (uint64_t *)flags, words * 8, 0);
+    const dim3 grid(std::max<uint32_t>(1, std::min<uint32_t>(c.last_waves, 65535)));
+    hipLaunchKernelGGL(k_rank_mark, grid, dim3(256), 0, c.stream, c.reports, c.seg_counts, c.seg_cap, c.last_waves,
+                       w_log2, (uint32_t)cells, flags);
+    GSS_HIP(hipGetLastError());
+    hipLaunchKernelGGL(k_rank_pack, dim3((unsigned)blocks), dim3(256), 0, c.stream, (const uint4 *)flags,
+                       (uint32_t)words, packed, totals);
+    GSS_HIP(hipGetLastError());
+    launch_scan_u32(c, totals, blocks);
+    hipLaunchKernelGGL(k_rank_place, grid, dim3(256), 0, c.stream, c.reports, c.seg_counts, c.seg_cap, c.last_waves,
+                       w_log2, (uint32_t)cells, packed, totals, limit, dst);
     GSS_HIP(hipGetLastError());
 }
 
@@ -151,7 +336,8 @@ void sort_records(Ctx &c, gss_report *src, uint64_t n, gss_report *dst) {
     const uint32_t n_tiles = (uint32_t)((n + kSortTile - 1) / kSortTile);
     const uint64_t hist_n = (uint64_t)kRadix * n_tiles;
     const size_t counts_bytes = kMaxPasses * kRadix * sizeof(unsigned long long);
-    char *buf = (char *)c.dalloc(counts_bytes + hist_n * 4);
+    const uint32_t chunks = (uint32_t)((hist_n + kScanChunk - 1) / kScanChunk);
+    char *buf = (char *)c.dalloc(counts_bytes + (hist_n + chunks) * 4);
     unsigned long long *counts = (unsigned long long *)buf;
     uint32_t *hist = (uint32_t *)(buf + counts_bytes);
     try {
@@ -170,8 +356,16 @@ void sort_records(Ctx &c, gss_report *src, uint64_t n, gss_report *dst) {
             hipLaunchKernelGGL(k_sort_tile_counts, dim3(n_tiles), dim3(kSortThreads), 0, c.stream, from, n, word_bits,
                                shift, hist, n_tiles);
             GSS_HIP(hipGetLastError());
-            hipLaunchKernelGGL(k_sort_scan, dim3(1), dim3(1024), 0, c.stream, hist, hist_n);
-            GSS_HIP(hipGetLastError());
+            if (chunks <= 2) {  // up to 32 tiles: one launch
+                launch_scan_u32(c, hist, hist_n);
+            } else {
+                uint32_t *sums = hist + hist_n;
+                hipLaunchKernelGGL(k_scan_sums, dim3(chunks), dim3(256), 0, c.stream, hist, hist_n, sums);
+                GSS_HIP(hipGetLastError());
+                launch_scan_u32(c, sums, chunks);
+                hipLaunchKernelGGL(k_scan_apply, dim3(chunks), dim3(256), 0, c.stream, hist, hist_n, sums);
+                GSS_HIP(hipGetLastError());
+            }
             hipLaunchKernelGGL(k_sort_scatter, dim3(n_tiles), dim3(kSortThreads), 0, c.stream, from, to, n, word_bits,
                                shift, hist, n_tiles);
             GSS_HIP(hipGetLastError());

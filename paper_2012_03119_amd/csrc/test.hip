@@ -381,6 +381,54 @@ static void queue_stitch(Ctx &c, const Segments &sg, gss_report *dst, uint64_t n
 
 void queue_stitch(Ctx &c, gss_report *dst, uint64_t n) { queue_stitch(c, context_segments(c), dst, n); }
 
+// The first n of the ordered records into dst (device memory; the caller's when
+// dev).  Ranked from the segments when its workspace (`rank` bytes, at ws or
+// allocated here) is to be had; otherwise every kept record is stitched and
+// radix-sorted, and the first n copied.  With 10.1 M records of 4 M clauses x 16 words
+// the ranked order's kernels take 0.25 ms (mark 61 us, pack 15, place 157, clearing
+// 12), where the radix sort took 5.9 ms; the pass of delta, test and ordered fetch went
+// from 6.53 to 1.02 ms.
+static void fetch_sorted(Ctx &c, gss_report *dst, uint64_t n, bool dev, char *ws, uint64_t rank) {
+    if (rank) {
+        char *own = nullptr;
+        if (!ws) {
+            try {
+                ws = own = (char *)c.dalloc(rank);
+            } catch (const Error &) {  // no room: the radix sort needs less where the cells outnumber the records
+            }
+        }
+        if (ws) {
+            try {
+                rank_records(c, ws, dst, n);
+                if (own) c.sync();
+            } catch (...) {
+                (void)hipStreamSynchronize(c.stream);
+                c.dfree(own);
+                throw;
+            }
+            c.dfree(own);
+            return;
+        }
+    }
+    const uint64_t all = c.n_kept;
+    gss_report *st = (gss_report *)c.dalloc(all * sizeof(gss_report));
+    gss_report *so = nullptr;
+    try {
+        so = (dev && n == all) ? dst : (gss_report *)c.dalloc(all * sizeof(gss_report));
+        queue_stitch(c, st, all);
+        sort_records(c, st, all, so);
+        if (so != dst) GSS_HIP(hipMemcpyAsync(dst, so, n * sizeof(gss_report), hipMemcpyDeviceToDevice, c.stream));
+        c.sync();
+    } catch (...) {
+        (void)hipStreamSynchronize(c.stream);
+        c.dfree(st);
+        if (so != dst) c.dfree(so);
+        throw;
+    }
+    c.dfree(st);
+    if (so != dst) c.dfree(so);
+}
+
 }  // namespace gss
 
 using namespace gss;
@@ -461,26 +509,15 @@ extern "C" gss_status gss_fetch_reports(gss_ctx *ctx, gss_report *out, uint64_t 
     if (n) {
         GSS_REQUIRE(out != nullptr, GSS_ERR_INVALID_ARG, "null argument");
         const bool dev = is_device_pointer(out);
-        gss_report *dst = dev ? out : (gss_report *)c.device_stage(n * sizeof(gss_report));
+        // host records pass through the bulk staging; a small ordered fetch has its
+        // workspace behind them there
+        const uint64_t rank = (c.last_flags & GSS_TEST_SORTED) ? rank_bytes(c) : 0;
+        const size_t head = dev ? 0 : (n * sizeof(gss_report) + 255) / 256 * 256;
+        const bool staged = rank && head + rank <= std::max<size_t>(c.dstage_bytes, dev ? 0 : (size_t)1 << 20);
+        char *stage = dev && !staged ? nullptr : (char *)c.device_stage(head + (staged ? rank : 0));
+        gss_report *dst = dev ? out : (gss_report *)stage;
         if (c.last_flags & GSS_TEST_SORTED) {
-            // every kept record takes part in the order; the first n of it are returned
-            const uint64_t all = c.n_kept;
-            gss_report *st = (gss_report *)c.dalloc(all * sizeof(gss_report));
-            gss_report *so = (dev && n == all) ? dst : (gss_report *)c.dalloc(all * sizeof(gss_report));
-            try {
-                queue_stitch(c, st, all);
-                sort_records(c, st, all, so);
-                if (so != dst)
-                    GSS_HIP(hipMemcpyAsync(dst, so, n * sizeof(gss_report), hipMemcpyDeviceToDevice, c.stream));
-                c.sync();
-            } catch (...) {
-                (void)hipStreamSynchronize(c.stream);
-                c.dfree(st);
-                if (so != dst) c.dfree(so);
-                throw;
-            }
-            c.dfree(st);
-            if (so != dst) c.dfree(so);
+            fetch_sorted(c, dst, n, dev, staged ? stage + head : nullptr, rank);
         } else {
             queue_stitch(c, dst, n);
         }
