@@ -12,6 +12,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import sys
 from typing import Optional
 
 import numpy as np
@@ -391,9 +392,23 @@ def gss_fetch_reports(ctx, cap: int) -> np.ndarray:
     return out[:n.value]
 
 
+def _settle_outputs() -> None:
+    """Waits for torch's current stream before the context's stream writes a device
+    output.  The output's memory may be in use there still: torch hands a freed
+    tensor's memory out again at once, since it orders only its own stream, while
+    kernels queued on that stream have yet to read the old tensor."""
+    torch = sys.modules.get("torch")
+    if torch is not None and torch.cuda.is_initialized():
+        cur = torch.cuda.current_stream()
+        if not cur.query():
+            cur.synchronize()
+
+
 def gss_fetch_reports_into(ctx, ptr: int, cap: int) -> int:
     """Copies up to cap records into memory at address ptr (device or host, room
-    for cap 16-byte records); returns how many were copied."""
+    for cap 16-byte records); returns how many were copied.  Device memory is
+    written behind the work queued on torch's current stream."""
+    _settle_outputs()
     n = ctypes.c_uint64()
     _check(ctx, load_library().gss_fetch_reports(ctx, ctypes.c_void_p(ptr), cap, ctypes.byref(n)))
     return n.value
@@ -720,6 +735,7 @@ class Context:
         if not (out.is_cuda and out.is_contiguous()):
             raise ValueError("out must be a contiguous CUDA tensor")
         cap = out.numel() * out.element_size() // 16
+        _settle_outputs()
         n = gss_test_noalloc(self.ctx, flags, out.data_ptr(), cap)
         self._held = []
         return n
