@@ -47,9 +47,9 @@ __device__ inline uint32_t lanes_per_clause(uint32_t RW) { return RW <= 4 ? 1u :
 
 template <int LPC, int WPL, int MODE, bool AGG>
 __device__ uint32_t batch_run(const StoreDesc &st, const TileRef &cur, gss_report *seg, uint32_t produced,
-                              uint32_t early_exit) {
+                              uint32_t early_exit, uint64_t *park) {
     using Ts = Tester<LPC, WPL, MODE, false, AGG>;
-    const Ts ts(threadIdx.x & 63, st.planes, st.active, st.W, 0, nullptr, 0u, st.agg, st.aggu);
+    const Ts ts(threadIdx.x & 63, park, st.planes, st.active, st.W, 0, nullptr, 0u, st.agg, st.aggu);
     Counts none;
     return ts.run(cur, seg, st.seg_cap, produced, early_exit, nullptr, none);
 }
@@ -78,6 +78,7 @@ __attribute__((amdgpu_waves_per_eu(MODE == 0 && !AGG ? 5 : 1))) void k_test_batc
                                                                          uint32_t n_segs, uint32_t total,
                                                                          uint32_t early_exit) {
     __shared__ uint32_t counts[kTestWavesPerBlock][kMaxBatch];  // records per (wavefront, store)
+    __shared__ uint64_t park[kTestWavesPerBlock][Tester<1, 4, MODE, false, AGG>::kParkWords];  // the widest lane's
     const uint32_t lane = threadIdx.x & 63, wib = threadIdx.x / 64;
     for (uint32_t s = lane; s < n_stores; s += 64) counts[wib][s] = 0;
     __syncthreads();
@@ -102,13 +103,13 @@ __attribute__((amdgpu_waves_per_eu(MODE == 0 && !AGG ? 5 : 1))) void k_test_batc
         gss_report *const seg = st.reports + (uint64_t)wave * st.seg_cap;
         uint32_t produced = counts[wib][s_cur];
         switch (st.RW) {
-        case 1: produced = batch_run<1, 1, MODE, AGG>(st, cur, seg, produced, early_exit); break;
-        case 2: produced = batch_run<1, 2, MODE, AGG>(st, cur, seg, produced, early_exit); break;
-        case 4: produced = batch_run<1, 4, MODE, AGG>(st, cur, seg, produced, early_exit); break;
-        case 8: produced = batch_run<2, 4, MODE, AGG>(st, cur, seg, produced, early_exit); break;
-        case 16: produced = batch_run<4, 4, MODE, AGG>(st, cur, seg, produced, early_exit); break;
-        case 32: produced = batch_run<8, 4, MODE, AGG>(st, cur, seg, produced, early_exit); break;
-        default: produced = batch_run<16, 4, MODE, AGG>(st, cur, seg, produced, early_exit); break;
+        case 1: produced = batch_run<1, 1, MODE, AGG>(st, cur, seg, produced, early_exit, park[wib]); break;
+        case 2: produced = batch_run<1, 2, MODE, AGG>(st, cur, seg, produced, early_exit, park[wib]); break;
+        case 4: produced = batch_run<1, 4, MODE, AGG>(st, cur, seg, produced, early_exit, park[wib]); break;
+        case 8: produced = batch_run<2, 4, MODE, AGG>(st, cur, seg, produced, early_exit, park[wib]); break;
+        case 16: produced = batch_run<4, 4, MODE, AGG>(st, cur, seg, produced, early_exit, park[wib]); break;
+        case 32: produced = batch_run<8, 4, MODE, AGG>(st, cur, seg, produced, early_exit, park[wib]); break;
+        default: produced = batch_run<16, 4, MODE, AGG>(st, cur, seg, produced, early_exit, park[wib]); break;
         }
         counts[wib][s_cur] = produced;
         g = gn;

@@ -24,7 +24,8 @@ __global__ __launch_bounds__(kTestWavesPerBlock * 64) void k_test(const BucketDe
         __syncthreads();
     }
     const uint32_t lane = threadIdx.x & 63;
-    const Ts ts(lane, a.planes, a.active, a.W, a.hot_rows, lds_rows, a.sched_run, a.agg, a.aggu, a.G, a.chunk_elems,
+    __shared__ uint64_t park[kTestWavesPerBlock][Ts::kParkWords];
+    const Ts ts(lane, park[threadIdx.x / 64], a.planes, a.active, a.W, a.hot_rows, lds_rows, a.sched_run, a.agg, a.aggu, a.G, a.chunk_elems,
                 a.n_rows, a.sagg, a.saggu);
     const uint32_t waves_per_block = blockDim.x / 64;
     const uint32_t n_waves = gridDim.x * waves_per_block;
@@ -97,7 +98,8 @@ __global__ __launch_bounds__(kTestWavesPerBlock * 64) void k_test_list(const Buc
     __syncthreads();
     constexpr uint32_t t_log2 = ilog2<Ts::T>();
     const uint32_t lane = threadIdx.x & 63, j = lane / LPC;
-    const Ts ts(lane, a.planes, a.active, a.W, a.hot_rows, lds_rows, 0u, a.agg, a.aggu);
+    __shared__ uint64_t park[kTestWavesPerBlock][Ts::kParkWords];
+    const Ts ts(lane, park[threadIdx.x / 64], a.planes, a.active, a.W, a.hot_rows, lds_rows, 0u, a.agg, a.aggu);
     const uint32_t waves_per_block = blockDim.x / 64;
     const uint32_t n_waves = gridDim.x * waves_per_block;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(xcd_remap(blockIdx.x, gridDim.x) * waves_per_block +

@@ -201,14 +201,17 @@ struct Tester {
     const uint64_t *sagg;   // G > 1: per code, super-groups with an F slot
     const uint64_t *saggu;  // G > 1, trigger mode: per variable, super-groups with an active U slot
     uint64_t n_rows;
+    // LDS words of a wavefront's join, and this lane's first one
+    static constexpr uint32_t kParkWords = 64 * WPL * (MODE == 1 ? 2 : 1);
+    uint64_t *park;
 
-    __device__ Tester(uint32_t lane, const uint64_t *planes, const uint64_t *active_, uint32_t W_, uint32_t hot_rows_,
+    __device__ Tester(uint32_t lane, uint64_t *wave_park, const uint64_t *planes, const uint64_t *active_, uint32_t W_, uint32_t hot_rows_,
                       const uint64_t *lds_, uint32_t sched_run_, const void *agg_, const void *aggu_, uint32_t G_ = 1,
                       uint64_t chunk_elems = 0, uint64_t n_rows_ = 0, const uint64_t *sagg_ = nullptr,
                       const uint64_t *saggu_ = nullptr)
         : j(lane / LPC), w0((lane % LPC) * WPL), W(W_), hot_rows(hot_rows_), sched_run(sched_run_), G(G_),
           active(active_), chunk_bytes(chunk_elems * 8), lds(lds_), agg(static_cast<const AggT *>(agg_)),
-          aggu(static_cast<const AggT *>(aggu_)), sagg(sagg_), saggu(saggu_), n_rows(n_rows_) {
+          aggu(static_cast<const AggT *>(aggu_)), sagg(sagg_), saggu(saggu_), n_rows(n_rows_), park(wave_park + lane) {
 #pragma unroll
         for (int i = 0; i < WPL; ++i) act[i] = (w0 + i < W) ? active[w0 + i] : 0;
         pbase = reinterpret_cast<const char *>(planes) + w0 * 8;
@@ -288,6 +291,137 @@ struct Tester {
         return af | ou;
     }
 
+    // ---- Long survivors.  A clause that is hit reads every literal, up to 65536, one
+    //      row after the other: with one clause in a hundred hit, these chains (300
+    //      rows, 150 us) were the whole duration of a test of less than a million
+    //      clauses, and the last third of the test of 4 M.  Once few clauses of a
+    //      wavefront are live, the wavefront joins them one at a time: its T lane
+    //      groups take T different literals of the clause in a step, and their
+    //      products are combined by shuffles.  The recurrence over literals (allFalse,
+    //      oneUndef) is a product of per-literal pairs (F, U) that may be taken in any
+    //      order: (a, o)(a', o') = (a & a', (o & a') | (a & o')).  Rows are read only
+    //      for the lanes' words that are live, so a hit reads no more than before; a
+    //      clause about to die may read rows in vain, so joining starts where the
+    //      chance survivors are gone (0.8% of clauses live after 12 literals at the
+    //      densities of the paper-scale workload, in trigger mode after 16), and ends
+    //      with its first step for a clause that its product kills (reading every
+    //      row of the chance survivors made a test without hits 15% slower).
+    //      Kernel times without and with it, one clause in a hundred hit: 4 M clauses
+    //      x 1024 slots 737 and 535 us (trigger mode 1385 and 1102), 1 M x 320 trigger
+    //      279 and 129, 700 K x 448 193 and 101, 20 K x 64 49 and 14.  Starting at 8
+    //      read more than it saved (592 us at 4 M), at 16 it was no better (534).
+    //      With the aggregate pre-test a chain is a quarter as long (four rows in
+    //      flight) and the registers cost a wavefront per SIMD (113 -> 131 us on
+    //      2 M clauses x 2048 correlated slots): no joining there.
+    static constexpr uint32_t kJoinFrom = MODE == 0 ? 12 : 16;
+
+    // Joining n clauses takes about (rem / T + 2) steps each, the chain up to rem
+    // (at least half of it: a length class spans a factor of two).
+    __device__ static bool joins(uint64_t live, uint32_t rem) {
+        uint64_t m = live;
+#pragma unroll
+        for (uint32_t d = 1; d < (uint32_t)LPC; d <<= 1) m |= m >> d;
+        uint32_t n = 0;  // clauses with a live lane: the first lane of each group has heard of all
+        if constexpr (LPC == 1) n = __builtin_popcountll(m);
+        else if constexpr (LPC == 2) n = __builtin_popcountll(m & 0x5555555555555555ull);
+        else if constexpr (LPC == 4) n = __builtin_popcountll(m & 0x1111111111111111ull);
+        else if constexpr (LPC == 8) n = __builtin_popcountll(m & 0x0101010101010101ull);
+        else n = __builtin_popcountll(m & 0x0001000100010001ull);
+        return 2 * n * ((rem + T - 1) / T + 2) < rem;
+    }
+
+    // Finishes the live clauses of the wavefront from literal k on (live: the lanes
+    // with a live word); all lanes call it.  The lanes' own words wait in LDS
+    // meanwhile (each lane touches its own entries only): 76 registers in the plain
+    // kernel, 6 wavefronts per SIMD; it held 72 and 7 before, and forcing 7 with the
+    // spills that takes measured no faster.
+    __device__ void join(const Tile &cur, const char *pb, uint64_t live, uint32_t k, uint32_t len, uint64_t (&af)[WPL],
+                         uint64_t (&ou)[WPL], uint32_t early_exit, Counts &cnt) const {
+        const uint32_t lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+        const uint32_t sub = lane % LPC;
+#pragma unroll
+        for (int i = 0; i < WPL; ++i) {
+            park[i * 64] = af[i];
+            if constexpr (MODE == 1) park[(WPL + i) * 64] = ou[i];
+        }
+        asm volatile("" ::: "memory");  // not forwarded past the loop in registers
+        while (live) {
+            const uint32_t first = (uint32_t)__builtin_ctzll(live) / LPC * LPC;  // the clause's first lane (uniform)
+            uint64_t mine = (live >> first) & ((1ull << LPC) - 1);               // its lanes with a live word
+            live &= ~(mine << first);
+            const uint32_t n = __builtin_amdgcn_readlane(len, first);
+            const uint32_t off = __builtin_amdgcn_readlane(cur.code_off, first);
+            // literal p's code: group p / 4 of the clause, the groups T * 16 bytes
+            // apart (past the clause's end its last one, not used)
+            auto code_at = [&](uint32_t p) -> uint32_t {
+                p = min(p, n - 1);
+                return __builtin_amdgcn_raw_buffer_load_b32(cur.lits, off + (p >> 2) * (T * 16u) + (p & 3u) * 4u, 0, 0);
+            };
+            uint32_t code = code_at(k + j);
+            // the first step's product tells the chance survivors, which end there
+            for (uint32_t p0 = k, stop = k + T;; stop = n) {
+                uint64_t a[WPL], o[WPL];
+#pragma unroll
+                for (int i = 0; i < WPL; ++i) {
+                    a[i] = ~0ull;
+                    o[i] = 0;
+                }
+                for (; p0 < min(stop, n); p0 += T) {
+                    const uint32_t next = code_at(p0 + T + j);  // in flight during this step's rows
+                    const bool reads = ((mine >> sub) & 1u) && p0 + j < n;
+                    if (cnt.on) cnt.gathers += (uint32_t)__builtin_popcountll(__ballot(reads));
+                    if (reads) {
+                        const Words<WPL> f = gather(pb, code);
+                        if constexpr (MODE == 1) {
+                            const Words<WPL> t = gather(pb, code ^ 1u);
+#pragma unroll
+                            for (int i = 0; i < WPL; ++i) o[i] = (a[i] & ~(f.v[i] | t.v[i])) | (o[i] & f.v[i]);
+                        }
+#pragma unroll
+                        for (int i = 0; i < WPL; ++i) a[i] &= f.v[i];
+                    }
+                    code = next;
+                }
+#pragma unroll
+                for (uint32_t d = LPC; d < 64; d <<= 1) {
+#pragma unroll
+                    for (int i = 0; i < WPL; ++i) {
+                        const uint64_t a2 = __shfl_xor((unsigned long long)a[i], d);
+                        if constexpr (MODE == 1) {
+                            const uint64_t o2 = __shfl_xor((unsigned long long)o[i], d);
+                            o[i] = (o[i] & a2) | (a[i] & o2);
+                        }
+                        a[i] &= a2;
+                    }
+                }
+                bool alive = false;
+                if (lane - first < (uint32_t)LPC) {  // the clause's own lanes take the product
+                    uint64_t any = 0;
+#pragma unroll
+                    for (int i = 0; i < WPL; ++i) {
+                        if constexpr (MODE == 1) {
+                            const uint64_t u = (park[(WPL + i) * 64] & a[i]) | (park[i * 64] & o[i]);
+                            park[(WPL + i) * 64] = u;
+                            any |= u;
+                        }
+                        const uint64_t w = park[i * 64] & a[i];
+                        park[i * 64] = w;
+                        any |= w;
+                    }
+                    alive = !early_exit || any != 0;
+                }
+                asm volatile("" ::: "memory");
+                mine &= __ballot(alive) >> first;
+                if (p0 >= n || !mine) break;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < WPL; ++i) {
+            af[i] = park[i * 64];
+            if constexpr (MODE == 1) ou[i] = park[(WPL + i) * 64];
+        }
+    }
+
     // Tests the clauses of an opened tile on chunk g of the rows.  Records go to
     // seg (capacity seg_cap) after the `produced` records already there; returns
     // the new count.  With dense != nullptr, writes each clause's mask row there
@@ -321,7 +455,14 @@ struct Tester {
                 uint64_t any = 0;
 #pragma unroll
                 for (int i = 0; i < WPL; ++i) any |= af[i] | ou[i];
-                if (!__ballot(lane_ok && k < len && (!early_exit || any != 0))) break;
+                const uint64_t live = __ballot(lane_ok && k < len && (!early_exit || any != 0));
+                if (!live) break;
+                if constexpr (!AGG) {
+                    if (k >= kJoinFrom && joins(live, S - k)) {
+                        join(cur, pb, live, k, len, af, ou, early_exit, cnt);
+                        break;
+                    }
+                }
             }
             uint4 cn = make_uint4(0, 0, 0, 0);
             if (k + 4 < S) {  // uniform branch: the next four codes, in flight during this group
