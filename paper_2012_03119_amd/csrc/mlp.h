@@ -5,9 +5,8 @@
 // the GPU).  Parameters are packed as W1[12][64] (input major), b1[64],
 // W2[64][64], b2[64], w3[64], b3: 5057 floats.
 //
-// Every sample is one lane.  The parameters are read at addresses that are the
-// same for the whole wavefront, so they come through the scalar data cache into
-// SGPRs and each multiply-add takes its weight as a scalar operand.
+// Every product runs on the matrix cores in fp32 (v_mfma_f32): the dense fp32 rate
+// there is twice the vector units' without packed instructions.
 #pragma once
 
 #include "gss_internal.h"
@@ -26,45 +25,91 @@ constexpr int kOffB3 = kOffW3 + kHid;
 constexpr int kParams = kOffB3 + 1;  // 5057
 static_assert(kParams == 5057, "parameter layout");
 
-// First layer: h1 = relu(x W1 + b1).
-__device__ inline void mlp_layer1(const float *__restrict__ p, const float (&x)[kFeat], float (&h1)[kHid]) {
-#pragma unroll
-    for (int j = 0; j < kHid; ++j) {
-        float a = p[kOffB1 + j];
-#pragma unroll
-        for (int i = 0; i < kFeat; ++i) a = fmaf(x[i], p[kOffW1 + i * kHid + j], a);
-        h1[j] = fmaxf(a, 0.f);
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+// Inference, 32 samples a wavefront step, with 32x32 outputs and K = 2 per
+// instruction on the transposed activations: H1^T = W1^T X^T (K = the 12 features),
+// then H2^T = W2^T H1^T (K = the 64 hidden units).  In the 32x32 result a lane holds
+// one sample (its column, lane % 32) and 16 rows; those are exactly the values that
+// lane must supply as the B operand (one K row for one sample) of the next product,
+// so the activations never move between lanes: step s of the second product takes
+// its two K rows from register s % 16 of tile s / 16 of the two lane halves, and the
+// weights (the A operand) are loaded in that same row order.  The output layer sums
+// each lane's 32 rows and its partner lane's (lane ^ 32).  The weights stay in
+// registers for all of a wavefront's steps, the biases and output weights in LDS.
+
+// row of the 32x32 result held in register v by a lane of half `half`
+__device__ constexpr uint32_t mfma_row(uint32_t v, uint32_t half) { return 8 * (v / 4) + 4 * half + (v % 4); }
+
+struct MlpBiases {  // in LDS
+    float b1[kHid], b2[kHid], w3[kHid];
+    __device__ void load(const float *__restrict__ p) {  // by a workgroup; a barrier follows
+        for (uint32_t t = threadIdx.x; t < kHid; t += blockDim.x) {
+            b1[t] = p[kOffB1 + t];
+            b2[t] = p[kOffB2 + t];
+            w3[t] = p[kOffW3 + t];
+        }
     }
-}
+};
 
-// Second layer, 16 outputs at a time: h2[c..c+16) = relu(h1 W2 + b2).
-template <int C>
-__device__ inline void mlp_layer2_chunk(const float *__restrict__ p, const float (&h1)[kHid], float (&h2)[16]) {
+struct MlpWeights {  // one lane's operands
+    float w1a[2][kFeat / 2], w2a[2][kHid / 2], b3;
+    __device__ void load(const float *__restrict__ p, uint32_t half, uint32_t col) {
 #pragma unroll
-    for (int k = 0; k < 16; ++k) h2[k] = p[kOffB2 + C + k];
+        for (uint32_t u = 0; u < 2; ++u) {
 #pragma unroll
-    for (int i = 0; i < kHid; ++i)
+            for (uint32_t st = 0; st < kFeat / 2; ++st) w1a[u][st] = p[kOffW1 + (2 * st + half) * kHid + 32 * u + col];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) h2[k] = fmaf(h1[i], p[kOffW2 + i * kHid + C + k], h2[k]);
-#pragma unroll
-    for (int k = 0; k < 16; ++k) h2[k] = fmaxf(h2[k], 0.f);
-}
+            for (uint32_t st = 0; st < kHid / 2; ++st) {
+                const uint32_t hid = 32 * (st / 16) + mfma_row(st % 16, half);
+                w2a[u][st] = p[kOffW2 + hid * kHid + 32 * u + col];
+            }
+        }
+        b3 = p[kOffB3];
+    }
+};
 
-// The output logit z3 of one sample.
-__device__ inline float mlp_logit(const float *__restrict__ p, const float (&x)[kFeat]) {
-    float h1[kHid];
-    mlp_layer1(p, x, h1);
-    float z3 = p[kOffB3];
-    float h2[16];
-#define GSS_MLP_CHUNK(C)                                                        \
-    mlp_layer2_chunk<C>(p, h1, h2);                                             \
-    _Pragma("unroll") for (int k = 0; k < 16; ++k) z3 = fmaf(h2[k], p[kOffW3 + C + k], z3);
-    GSS_MLP_CHUNK(0)
-    GSS_MLP_CHUNK(16)
-    GSS_MLP_CHUNK(32)
-    GSS_MLP_CHUNK(48)
-#undef GSS_MLP_CHUNK
-    return z3;
+// The output logit of the lane's sample (both halves of the wavefront get it).
+// xh[st]: feature 2 st + half of sample `col`.
+__device__ inline float mlp_tile_logit(const MlpWeights &w, const MlpBiases &s, const float (&xh)[kFeat / 2],
+                                       uint32_t half) {
+    // an index the compiler cannot see through: the LDS reads stay in the
+    // caller's loop instead of being hoisted into 96 more registers per lane
+    uint32_t lds_row = 4 * half;
+    asm volatile("" : "+v"(lds_row));
+    f32x16 acc1[2], acc2[2];
+#pragma unroll
+    for (uint32_t u = 0; u < 2; ++u)
+#pragma unroll
+        for (uint32_t v = 0; v < 16; ++v) {
+            const uint32_t row = 32 * u + 8 * (v / 4) + (v % 4) + lds_row;  // mfma_row(v, half)
+            acc1[u][v] = s.b1[row];
+            acc2[u][v] = s.b2[row];
+        }
+#pragma unroll
+    for (uint32_t st = 0; st < kFeat / 2; ++st)
+#pragma unroll
+        for (uint32_t u = 0; u < 2; ++u)
+            acc1[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(w.w1a[u][st], xh[st], acc1[u], 0, 0, 0);
+#pragma unroll
+    for (uint32_t u = 0; u < 2; ++u)
+#pragma unroll
+        for (uint32_t v = 0; v < 16; ++v) acc1[u][v] = fmaxf(acc1[u][v], 0.f);
+#pragma unroll
+    for (uint32_t st = 0; st < kHid / 2; ++st) {
+        const float bh = acc1[st / 16][st % 16];
+#pragma unroll
+        for (uint32_t u = 0; u < 2; ++u)
+            acc2[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(w.w2a[u][st], bh, acc2[u], 0, 0, 0);
+    }
+    float part = 0.f;
+#pragma unroll
+    for (uint32_t u = 0; u < 2; ++u)
+#pragma unroll
+        for (uint32_t v = 0; v < 16; ++v)
+            part = fmaf(fmaxf(acc2[u][v], 0.f), s.w3[32 * u + 8 * (v / 4) + (v % 4) + lds_row], part);
+    return part + __shfl_xor(part, 32) + w.b3;
 }
 
 __device__ inline float sigmoidf_(float z) { return 1.f / (1.f + expf(-z)); }
@@ -97,15 +142,22 @@ struct MlpWork {
     uint64_t step = 0;          // Adam steps taken with the current moments
 };
 
-constexpr uint32_t kGradSamples = 32;  // samples per workgroup of the gradient kernel
+constexpr uint32_t kGradSamples = 16;  // samples per group of the gradient kernel
+constexpr uint32_t kGradBlocks = 256;  // its workgroups at most, each with a partial gradient
 
 // Queues the gradient of the mean loss over n samples (rows order[first..first+n)
 // of x/y, or rows first..first+n when order is null) into w.grad, its loss into
 // w.loss; inv_n scales both.
 void mlp_queue_grad(Ctx &c, MlpWork &w, const float *x, const float *y, const uint32_t *order, uint64_t first,
                     uint32_t n);
-// Queues one Adam step on w.params from w.grad.
-void mlp_queue_adam(Ctx &c, MlpWork &w, float lr, float beta1, float beta2, float eps);
+// Queues the same gradient and one Adam step on w.params from it; the loss goes to
+// *loss (device).
+void mlp_queue_step(Ctx &c, MlpWork &w, const float *x, const float *y, const uint32_t *order, uint64_t first,
+                    uint32_t n, float lr, float beta1, float beta2, float eps, float *loss);
+// Workgroups of 4 wavefronts for inference on n samples, 32 per wavefront step; at
+// most 2 workgroups per compute unit, as many as are resident with the weights in
+// registers (4 M samples in 362 us a call; with 1 411, with 3 373, with 4 361).
+unsigned mlp_grid(const Ctx &c, uint64_t n);
 MlpWork &mlp_work(Ctx &c);
 void mlp_release(Ctx &c);
 char *mlp_stage(Ctx &c, MlpWork &w, size_t bytes);

@@ -1,13 +1,5 @@
 // Kernels and entry points of the clause-priority network (mlp.h): batched
 // inference, the gradient of the mean binary cross-entropy, and Adam.
-//
-// Gradient: a workgroup of 64 lanes takes 32 samples.  Each of the first 32
-// lanes runs one sample forward and backward and leaves its activations and
-// deltas in LDS (rows padded to 65 floats, so that the lanes' row writes fall in
-// different banks); then lane t accumulates column t of every weight gradient
-// over the 32 samples (the sample's activation is read by all lanes at once, a
-// broadcast).  Each workgroup writes one partial gradient row; a second kernel
-// sums the rows in a fixed order, so the result does not depend on scheduling.
 #include "mlp.h"
 
 #include <algorithm>
@@ -17,128 +9,210 @@
 
 namespace gss {
 
+// 32 samples a wavefront step (mlp_tile_logit); the next step's features are loaded
+// while the current one multiplies.  Bound by the fp32 matrix rate: 76 instructions
+// of 64 cycles for 32 samples, 31 us for 500 K samples on 1024 SIMDs at 2.4 GHz.
+// 500 K samples: 56 us (a sample a lane with fp32 vector multiply-adds and scalar
+// weights: 100 us); the call 121 -> 74 us, with 1000 samples 81 -> 30 us.
 __global__ __launch_bounds__(256) void k_mlp_forward(const float *__restrict__ p, const float *__restrict__ x,
                                                      uint32_t n, float *__restrict__ out) {
-    const uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= n) return;
-    float xv[kFeat];
+    __shared__ MlpBiases bias;
+    bias.load(p);
+    __syncthreads();
+    const uint32_t lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
+    MlpWeights w;
+    w.load(p, half, col);
+    const uint64_t step = (uint64_t)gridDim.x * (blockDim.x / 64) * 32;
+    uint64_t base = ((uint64_t)blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64) * 32;
+    // past the end a lane reads the last sample's features and stores nothing
+    auto features = [&](uint64_t b, float (&v)[kFeat / 2]) {
+        const float *src = x + min(b + col, (uint64_t)n - 1) * kFeat + half;
 #pragma unroll
-    for (int k = 0; k < kFeat; ++k) xv[k] = x[(uint64_t)s * kFeat + k];
-    out[s] = sigmoidf_(mlp_logit(p, xv));
+        for (uint32_t st = 0; st < kFeat / 2; ++st) v[st] = src[2 * st];
+    };
+    float cur[kFeat / 2];
+    features(base, cur);
+    for (; base < n; base += step) {
+        float nxt[kFeat / 2];
+        features(base + step, nxt);
+        const float z = mlp_tile_logit(w, bias, cur, half);
+        if (half == 0 && base + col < n) out[base + col] = sigmoidf_(z);
+#pragma unroll
+        for (uint32_t st = 0; st < kFeat / 2; ++st) cur[st] = nxt[st];
+    }
 }
 
-__global__ __launch_bounds__(64) void k_mlp_grad(const float *__restrict__ p, const float *__restrict__ x,
-                                                 const float *__restrict__ y, const uint32_t *__restrict__ order,
-                                                 uint64_t first, uint32_t n, float inv_n, float *__restrict__ partials) {
-    constexpr int B = kGradSamples, LD = kHid + 1;
-    __shared__ float sx[B][kFeat + 1];
-    __shared__ float sh1[B][LD], sh2[B][LD], sdz2[B][LD], sdz1[B][LD];
-    __shared__ float sdz3[B], sloss[B];
-    const uint32_t t = threadIdx.x;
-    if (t < B) {
-        const uint64_t s = (uint64_t)blockIdx.x * B + t;
-        const bool ok = s < n;
-        float xv[kFeat], yv = 0.f;
-        if (ok) {
-            const uint64_t row = order ? order[first + s] : first + s;
+// Gradient: a workgroup of four wavefronts takes groups of 16 samples and runs them
+// forward and backward on 16x16 fp32 matrix tiles, wavefront w owning hidden units
+// 16 w .. 16 w + 15 of both layers.  In a result tile a lane holds samples 4 g .. 4 g
+// + 3 (g = lane / 16) of unit 16 w + lane % 16, so the ReLU masks of the backward
+// pass are read from the registers of the forward one; the activations and deltas
+// the next product needs as operands go through LDS.  The first layer's bias is its
+// 13th input row (x = 1), which gives its gradient with the weights'.  The weight
+// gradients stay in registers over the workgroup's groups; each workgroup writes one
+// partial gradient, and k_mlp_reduce sums them in a fixed order, so the result does
+// not depend on scheduling.
+//
+// A batch of 1024 samples is 64 workgroups of one group: bound by the chain of five
+// products and their barriers, 7.6 us (a sample a lane with the two layers' 5000
+// multiply-adds in sequence, 32 lanes of each workgroup busy: 119 us).
+__global__ __launch_bounds__(256) void k_mlp_grad(const float *__restrict__ p, const float *__restrict__ x,
+                                                  const float *__restrict__ y, const uint32_t *__restrict__ order,
+                                                  uint64_t first, uint32_t n, float inv_n, float *__restrict__ partials) {
+    // row strides: operand reads take rows lane % 16 (stride 4 mod 64: banks 4 i + g)
+    // or rows g (any), and W2 by rows g (stride 16 mod 64: banks 16 g + i)
+    constexpr int B = kGradSamples, LW = 80, LH = 68, LX = 20;
+    __shared__ float w2[kHid][LW];
+    __shared__ float sx[B][LX], sh1[B][LH], sd2[B][LH], sd1[B][LH];
+    __shared__ float sz[4][B], sy[B], sdz3[B];
+    const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6, i = lane & 15, g = lane >> 4;
+    const uint32_t unit = 16 * wave + i;
 #pragma unroll
-            for (int k = 0; k < kFeat; ++k) xv[k] = x[row * kFeat + k];
-            yv = y[row];
-        } else {
-#pragma unroll
-            for (int k = 0; k < kFeat; ++k) xv[k] = 0.f;
-        }
-        float h1[kHid];
-        mlp_layer1(p, xv, h1);
-        float z3 = p[kOffB3];
-        float h2[16];
-#define GSS_MLP_CHUNK(C)                                                        \
-        mlp_layer2_chunk<C>(p, h1, h2);                                         \
-        _Pragma("unroll") for (int k = 0; k < 16; ++k) {                        \
-            sh2[t][C + k] = h2[k];                                              \
-            z3 = fmaf(h2[k], p[kOffW3 + C + k], z3);                            \
-        }
-        GSS_MLP_CHUNK(0)
-        GSS_MLP_CHUNK(16)
-        GSS_MLP_CHUNK(32)
-        GSS_MLP_CHUNK(48)
-#undef GSS_MLP_CHUNK
-        const float dz3 = ok ? (sigmoidf_(z3) - yv) * inv_n : 0.f;
-        sdz3[t] = dz3;
-        sloss[t] = ok ? bce_logit(z3, yv) * inv_n : 0.f;
-        float dz2[kHid];
-#pragma unroll
-        for (int j = 0; j < kHid; ++j) {
-            dz2[j] = sh2[t][j] > 0.f ? dz3 * p[kOffW3 + j] : 0.f;
-            sdz2[t][j] = dz2[j];
-        }
-#pragma unroll
-        for (int i = 0; i < kHid; ++i) {
-            float a = 0.f;
-#pragma unroll
-            for (int j = 0; j < kHid; ++j) a = fmaf(dz2[j], p[kOffW2 + i * kHid + j], a);
-            sdz1[t][i] = h1[i] > 0.f ? a : 0.f;
-            sh1[t][i] = h1[i];
-        }
-#pragma unroll
-        for (int k = 0; k < kFeat; ++k) sx[t][k] = xv[k];
+    for (uint32_t k = 0; k < kHid * kHid / 256; ++k) {
+        const uint32_t e = t + 256 * k;
+        w2[e / kHid][e % kHid] = p[kOffW2 + e];
     }
-    __syncthreads();
-    float gw2[kHid], gw1[kFeat];
+    float w1[4];  // rows 4 s + g of (W1, b1, 0, 0, 0)
 #pragma unroll
-    for (int i = 0; i < kHid; ++i) gw2[i] = 0.f;
+    for (uint32_t s = 0; s < 4; ++s) {
+        const uint32_t k = 4 * s + g;
+        w1[s] = k < (uint32_t)kFeat ? p[kOffW1 + k * kHid + unit] : k == (uint32_t)kFeat ? p[kOffB1 + unit] : 0.f;
+    }
+    const float b2 = p[kOffB2 + unit], w3 = p[kOffW3 + unit], b3 = p[kOffB3];
+    f32x4 gw2[4], gw1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int k = 0; k < kFeat; ++k) gw1[k] = 0.f;
-    float gb1 = 0.f, gb2 = 0.f, gw3 = 0.f, gb3 = 0.f, gl = 0.f;
-    for (int s = 0; s < B; ++s) {
-        const float d2 = sdz2[s][t], d1 = sdz1[s][t];
+    for (int q = 0; q < 4; ++q) gw2[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float gb2 = 0.f, gw3 = 0.f, gb3 = 0.f, gl = 0.f;
+    const uint32_t groups = (n + B - 1) / B;
+    for (uint32_t grp = blockIdx.x; grp < groups; grp += gridDim.x) {
+        {  // 16 rows of 12 features, a one and three zeros; a lane of the zeros fetches the label
+            const uint32_t r = t >> 4, k = t & 15;
+            const uint64_t s = (uint64_t)grp * B + r;
+            const bool ok = s < n;
+            const uint64_t row = !ok ? 0 : order ? order[first + s] : first + s;
+            sx[r][k] = k < (uint32_t)kFeat ? (ok ? x[row * kFeat + k] : 0.f) : k == (uint32_t)kFeat ? 1.f : 0.f;
+            if (k == 15) sy[r] = ok ? y[row] : 0.f;
+        }
+        __syncthreads();
+        f32x4 a = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int i = 0; i < kHid; ++i) gw2[i] = fmaf(sh1[s][i], d2, gw2[i]);
+        for (uint32_t s = 0; s < 4; ++s) a = __builtin_amdgcn_mfma_f32_16x16x4f32(sx[i][4 * s + g], w1[s], a, 0, 0, 0);
+        float h1[4], h2[4];
 #pragma unroll
-        for (int k = 0; k < kFeat; ++k) gw1[k] = fmaf(sx[s][k], d1, gw1[k]);
-        gb1 += d1;
-        gb2 += d2;
-        gw3 = fmaf(sdz3[s], sh2[s][t], gw3);
-        gb3 += sdz3[s];
-        gl += sloss[s];
+        for (uint32_t r = 0; r < 4; ++r) {
+            h1[r] = fmaxf(a[r], 0.f);
+            sh1[4 * g + r][unit] = h1[r];
+        }
+        __syncthreads();
+        f32x4 c = {b2, b2, b2, b2};
+#pragma unroll
+        for (uint32_t s = 0; s < kHid / 4; ++s)
+            c = __builtin_amdgcn_mfma_f32_16x16x4f32(sh1[i][4 * s + g], w2[4 * s + g][unit], c, 0, 0, 0);
+#pragma unroll
+        for (uint32_t r = 0; r < 4; ++r) {
+            h2[r] = fmaxf(c[r], 0.f);
+            float z = h2[r] * w3;  // summed over the wavefront's 16 units
+#pragma unroll
+            for (uint32_t d = 1; d < 16; d <<= 1) z += __shfl_xor(z, d);
+            if (i == 0) sz[wave][4 * g + r] = z;
+        }
+        __syncthreads();
+        if (t < (uint32_t)B) {
+            const bool ok = (uint64_t)grp * B + t < n;
+            const float z = b3 + ((sz[0][t] + sz[1][t]) + (sz[2][t] + sz[3][t]));
+            const float d = ok ? (sigmoidf_(z) - sy[t]) * inv_n : 0.f;
+            sdz3[t] = d;
+            gb3 += d;
+            gl += ok ? bce_logit(z, sy[t]) * inv_n : 0.f;
+        }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t r = 0; r < 4; ++r) {
+            const float d3 = sdz3[4 * g + r];
+            const float d2 = h2[r] > 0.f ? d3 * w3 : 0.f;
+            sd2[4 * g + r][unit] = d2;
+            gb2 += d2;
+            gw3 = fmaf(d3, h2[r], gw3);
+        }
+        __syncthreads();
+        f32x4 e = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (uint32_t s = 0; s < kHid / 4; ++s)
+            e = __builtin_amdgcn_mfma_f32_16x16x4f32(sd2[i][4 * s + g], w2[unit][4 * s + g], e, 0, 0, 0);
+#pragma unroll
+        for (uint32_t r = 0; r < 4; ++r) sd1[4 * g + r][unit] = h1[r] > 0.f ? e[r] : 0.f;
+#pragma unroll
+        for (uint32_t s = 0; s < B / 4; ++s) {  // rows `unit` of W2's gradient, all 64 columns
+            const float h = sh1[4 * s + g][unit];
+#pragma unroll
+            for (uint32_t q = 0; q < 4; ++q)
+                gw2[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(h, sd2[4 * s + g][16 * q + i], gw2[q], 0, 0, 0);
+        }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t s = 0; s < B / 4; ++s)
+            gw1 = __builtin_amdgcn_mfma_f32_16x16x4f32(sx[4 * s + g][i], sd1[4 * s + g][unit], gw1, 0, 0, 0);
+        __syncthreads();  // the next group overwrites sx
     }
     float *out = partials + (uint64_t)blockIdx.x * (kParams + 1);
 #pragma unroll
-    for (int i = 0; i < kHid; ++i) out[kOffW2 + i * kHid + t] = gw2[i];
+    for (uint32_t r = 0; r < 4; ++r) {
+        const uint32_t row = 4 * g + r;
 #pragma unroll
-    for (int k = 0; k < kFeat; ++k) out[kOffW1 + k * kHid + t] = gw1[k];
-    out[kOffB1 + t] = gb1;
-    out[kOffB2 + t] = gb2;
-    out[kOffW3 + t] = gw3;
+        for (uint32_t q = 0; q < 4; ++q) out[kOffW2 + (16 * wave + row) * kHid + 16 * q + i] = gw2[q][r];
+        if (row < (uint32_t)kFeat) out[kOffW1 + row * kHid + unit] = gw1[r];
+        if (row == (uint32_t)kFeat) out[kOffB1 + unit] = gw1[r];
+    }
+    gb2 += __shfl_xor(gb2, 16);
+    gb2 += __shfl_xor(gb2, 32);
+    gw3 += __shfl_xor(gw3, 16);
+    gw3 += __shfl_xor(gw3, 32);
+    if (g == 0) {
+        out[kOffB2 + unit] = gb2;
+        out[kOffW3 + unit] = gw3;
+    }
+#pragma unroll
+    for (uint32_t d = 1; d < (uint32_t)B; d <<= 1) {  // lanes 0..15 of wavefront 0 hold the sums
+        gb3 += __shfl_xor(gb3, d);
+        gl += __shfl_xor(gl, d);
+    }
     if (t == 0) {
         out[kOffB3] = gb3;
         out[kParams] = gl;
     }
 }
 
-// grad[i] = sum over rows of partials[row][i], rows in order; entry kParams is the loss.
-__global__ void k_mlp_reduce(const float *__restrict__ partials, uint32_t rows, float *__restrict__ grad,
-                             float *__restrict__ loss) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i > (uint32_t)kParams) return;
+// The sum over rows of partials[row][i], entry kParams the loss: a workgroup takes 64
+// entries, its four wavefronts every fourth row, in a fixed order.  ADAM: the entry's
+// parameter takes its Adam step at once (a training step is two launches); otherwise
+// the sum goes to grad.  64 rows: 3.7 us with the Adam step (one thread summing the
+// 32 rows of an entry, a copy of the loss and Adam as launches of their own: 18 us).
+template <bool ADAM>
+__global__ __launch_bounds__(256) void k_mlp_reduce(const float *__restrict__ partials, uint32_t rows,
+                                                    float *__restrict__ grad, float *__restrict__ loss,
+                                                    float *__restrict__ p, float *__restrict__ m, float *__restrict__ v,
+                                                    float lr, float beta1, float beta2, float eps, float c1, float c2) {
+    __shared__ float part[4][64];
+    const uint32_t c = threadIdx.x & 63, wave = threadIdx.x >> 6, i = blockIdx.x * 64 + c;
+    const float *src = partials + min(i, (uint32_t)kParams);
     float a = 0.f;
-    for (uint32_t r = 0; r < rows; ++r) a += partials[(uint64_t)r * (kParams + 1) + i];
-    if (i < (uint32_t)kParams)
-        grad[i] = a;
-    else
-        *loss = a;
-}
-
-__global__ void k_mlp_adam(float *__restrict__ p, const float *__restrict__ g, float *__restrict__ m,
-                           float *__restrict__ v, float lr, float beta1, float beta2, float eps, float c1, float c2) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (uint32_t)kParams) return;
-    const float gi = g[i];
-    const float mi = beta1 * m[i] + (1.f - beta1) * gi;
-    const float vi = beta2 * v[i] + (1.f - beta2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+#pragma unroll 8
+    for (uint32_t r = wave; r < rows; r += 4) a += src[(uint64_t)r * (kParams + 1)];
+    part[wave][c] = a;
+    __syncthreads();
+    if (wave != 0 || i > (uint32_t)kParams) return;
+    const float gi = (part[0][c] + part[1][c]) + (part[2][c] + part[3][c]);
+    if (i == (uint32_t)kParams) {
+        *loss = gi;
+    } else if (!ADAM) {
+        grad[i] = gi;
+    } else {
+        const float mi = beta1 * m[i] + (1.f - beta1) * gi;
+        const float vi = beta2 * v[i] + (1.f - beta2) * gi * gi;
+        m[i] = mi;
+        v[i] = vi;
+        p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+    }
 }
 
 MlpWork &mlp_work(Ctx &c) {
@@ -183,9 +257,10 @@ char *mlp_stage(Ctx &c, MlpWork &w, size_t bytes) {
     return w.stage;
 }
 
-void mlp_queue_grad(Ctx &c, MlpWork &w, const float *x, const float *y, const uint32_t *order, uint64_t first,
-                    uint32_t n) {
-    const uint32_t blocks = (n + kGradSamples - 1) / kGradSamples;
+// Queues the partial gradients; returns their number.
+static uint32_t queue_partials(Ctx &c, MlpWork &w, const float *x, const float *y, const uint32_t *order, uint64_t first,
+                               uint32_t n) {
+    const uint32_t blocks = std::min<uint32_t>((n + kGradSamples - 1) / kGradSamples, kGradBlocks);
     if (blocks > w.partial_rows) {
         c.sync();
         c.dfree(w.partials);
@@ -195,21 +270,35 @@ void mlp_queue_grad(Ctx &c, MlpWork &w, const float *x, const float *y, const ui
         w.partials = (float *)c.dalloc((size_t)rows * (kParams + 1) * 4);
         w.partial_rows = rows;
     }
-    hipLaunchKernelGGL(k_mlp_grad, dim3(blocks), dim3(64), 0, c.stream, w.params, x, y, order, first, n, 1.f / n,
+    hipLaunchKernelGGL(k_mlp_grad, dim3(blocks), dim3(256), 0, c.stream, w.params, x, y, order, first, n, 1.f / n,
                        w.partials);
     GSS_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_mlp_reduce, dim3((kParams + 1 + 255) / 256), dim3(256), 0, c.stream, w.partials, blocks,
-                       w.grad, w.loss);
+    return blocks;
+}
+
+constexpr unsigned kReduceBlocks = (kParams + 1 + 63) / 64;
+
+void mlp_queue_grad(Ctx &c, MlpWork &w, const float *x, const float *y, const uint32_t *order, uint64_t first,
+                    uint32_t n) {
+    const uint32_t rows = queue_partials(c, w, x, y, order, first, n);
+    hipLaunchKernelGGL(k_mlp_reduce<false>, dim3(kReduceBlocks), dim3(256), 0, c.stream, w.partials, rows, w.grad, w.loss,
+                       nullptr, nullptr, nullptr, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f);
     GSS_HIP(hipGetLastError());
 }
 
-void mlp_queue_adam(Ctx &c, MlpWork &w, float lr, float beta1, float beta2, float eps) {
+void mlp_queue_step(Ctx &c, MlpWork &w, const float *x, const float *y, const uint32_t *order, uint64_t first,
+                    uint32_t n, float lr, float beta1, float beta2, float eps, float *loss) {
     w.step++;
     const double c1 = 1.0 - std::pow((double)beta1, (double)w.step);
     const double c2 = 1.0 - std::pow((double)beta2, (double)w.step);
-    hipLaunchKernelGGL(k_mlp_adam, dim3((kParams + 255) / 256), dim3(256), 0, c.stream, w.params, w.grad, w.m, w.v,
-                       lr, beta1, beta2, eps, (float)c1, (float)c2);
+    const uint32_t rows = queue_partials(c, w, x, y, order, first, n);
+    hipLaunchKernelGGL(k_mlp_reduce<true>, dim3(kReduceBlocks), dim3(256), 0, c.stream, w.partials, rows, nullptr, loss,
+                       w.params, w.m, w.v, lr, beta1, beta2, eps, (float)c1, (float)c2);
     GSS_HIP(hipGetLastError());
+}
+
+unsigned mlp_grid(const Ctx &c, uint64_t n) {
+    return (unsigned)std::max<uint64_t>(1, std::min<uint64_t>((n + 127) / 128, (uint64_t)c.n_cu * 2));
 }
 
 // Queues the upload of host parameters into w.params through the upload ring.
@@ -247,7 +336,7 @@ extern "C" gss_status gss_mlp_forward(gss_ctx *ctx, const float *params, const f
     const float *dx = (const float *)device_input(c, st, 0, x, (size_t)n * kFeat * 4);
     const bool dev_out = is_device_pointer(out);
     float *dout = dev_out ? out : (float *)(st + xb);
-    hipLaunchKernelGGL(k_mlp_forward, dim3((n + 255) / 256), dim3(256), 0, c.stream, w.params, dx, n, dout);
+    hipLaunchKernelGGL(k_mlp_forward, dim3(mlp_grid(c, n)), dim3(256), 0, c.stream, w.params, dx, n, dout);
     GSS_HIP(hipGetLastError());
     if (!dev_out) GSS_HIP(hipMemcpyAsync(out, dout, (size_t)n * 4, hipMemcpyDeviceToHost, c.stream));
     c.sync();
@@ -309,9 +398,7 @@ extern "C" gss_status gss_mlp_train(gss_ctx *ctx, float *params, const float *x,
     for (uint64_t k = 0; k < steps; ++k) {
         const uint64_t first = k * cfg->batch;
         const uint32_t nb = (uint32_t)std::min<uint64_t>(cfg->batch, n_order - first);
-        mlp_queue_grad(c, w, dx, dy, dorder, first, nb);
-        GSS_HIP(hipMemcpyAsync(dlosses + k, w.loss, 4, hipMemcpyDeviceToDevice, c.stream));
-        mlp_queue_adam(c, w, cfg->lr, cfg->beta1, cfg->beta2, cfg->eps);
+        mlp_queue_step(c, w, dx, dy, dorder, first, nb, cfg->lr, cfg->beta1, cfg->beta2, cfg->eps, dlosses + k);
     }
     GSS_HIP(hipMemcpyAsync(params, w.params, kParams * 4, hipMemcpyDeviceToHost, c.stream));
     if (out_losses) GSS_HIP(hipMemcpyAsync(out_losses, dlosses, steps * 4, hipMemcpyDeviceToHost, c.stream));
