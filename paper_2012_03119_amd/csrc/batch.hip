@@ -51,7 +51,7 @@ __device__ uint32_t batch_run(const StoreDesc &st, const TileRef &cur, gss_repor
     using Ts = Tester<LPC, WPL, MODE, false, AGG>;
     const Ts ts(threadIdx.x & 63, park, st.planes, st.active, st.W, 0, nullptr, 0u, st.agg, st.aggu);
     Counts none;
-    return ts.run(cur, seg, st.seg_cap, produced, early_exit, nullptr, none);
+    return ts.run(cur, seg, st.seg_cap, produced, early_exit, nullptr, false, none);
 }
 
 // The store and store-local tile of global tile g: segs[lo].begin <= g < segs[lo + 1].begin.
@@ -78,7 +78,7 @@ __attribute__((amdgpu_waves_per_eu(MODE == 0 && !AGG ? 5 : 1))) void k_test_batc
                                                                          uint32_t n_segs, uint32_t total,
                                                                          uint32_t early_exit) {
     __shared__ uint32_t counts[kTestWavesPerBlock][kMaxBatch];  // records per (wavefront, store)
-    __shared__ uint64_t park[kTestWavesPerBlock][Tester<1, 4, MODE, false, AGG>::kParkWords];  // the widest lane's
+    __shared__ __align__(16) uint64_t park[kTestWavesPerBlock][Tester<1, 4, MODE, false, AGG>::kParkWords];  // the widest lane's
     const uint32_t lane = threadIdx.x & 63, wib = threadIdx.x / 64;
     for (uint32_t s = lane; s < n_stores; s += 64) counts[wib][s] = 0;
     __syncthreads();

@@ -212,8 +212,11 @@ static void launch(Ctx &c, const Launch &L, uint32_t flags, const Segments &sg) 
     // of host time per launch, on the path between two tests)
     c.timed = serial % std::max<uint32_t>(1u, c.cfg.timing_interval) == 0;
     if (c.timed) GSS_HIP(hipEventRecord(c.ev_start, c.stream));
+    // records that will be ordered, or whose clauses' hits will be counted, come grouped
+    const bool grouped = (flags & GSS_TEST_SORTED) || c.prio;
     hipLaunchKernelGGL(L.fn, dim3(L.grid), dim3(kTestWavesPerBlock * 64), L.lds, c.stream, L.descs, L.args,
-                       (flags & GSS_TEST_NO_EARLY_EXIT) ? 0u : 1u, (flags & GSS_TEST_DENSE) ? 1u : 0u);
+                       (flags & GSS_TEST_NO_EARLY_EXIT) ? 0u : 1u,
+                       ((flags & GSS_TEST_DENSE) ? kOutDense : 0u) | (grouped ? kOutGrouped : 0u));
     GSS_HIP(hipGetLastError());
     if (c.timed) GSS_HIP(hipEventRecord(c.ev_stop, c.stream));
     const uint32_t n_waves = L.grid * kTestWavesPerBlock;

@@ -9,13 +9,17 @@
 
 namespace gss {
 
+// Bits of the test kernels' `out`: mask rows instead of records; a clause's records
+// side by side.
+constexpr uint32_t kOutDense = 1, kOutGrouped = 2;
+
 // Each wavefront walks the tiles t = wave, wave + N, ... (N wavefronts in the
 // grid) and prefetches the next tile's metadata and first codes while it tests
 // the current one.  WIDE: plane rows of more than 64 words (several chunks).
 template <int LPC, int WPL, int MODE, bool HOT, bool AGG, bool WIDE = false>
 __global__ __launch_bounds__(kTestWavesPerBlock * 64) void k_test(const BucketDesc *__restrict__ descs,
                                                                    const TestArgs a, uint32_t early_exit,
-                                                                   uint32_t dense) {
+                                                                   uint32_t out) {
     using Ts = Tester<LPC, WPL, MODE, HOT, AGG, WIDE>;
     extern __shared__ uint64_t lds_rows[];
     if constexpr (HOT) {
@@ -24,7 +28,7 @@ __global__ __launch_bounds__(kTestWavesPerBlock * 64) void k_test(const BucketDe
         __syncthreads();
     }
     const uint32_t lane = threadIdx.x & 63;
-    __shared__ uint64_t park[kTestWavesPerBlock][Ts::kParkWords];
+    __shared__ __align__(16) uint64_t park[kTestWavesPerBlock][Ts::kParkWords];
     const Ts ts(lane, park[threadIdx.x / 64], a.planes, a.active, a.W, a.hot_rows, lds_rows, a.sched_run, a.agg, a.aggu, a.G, a.chunk_elems,
                 a.n_rows, a.sagg, a.saggu);
     const uint32_t waves_per_block = blockDim.x / 64;
@@ -34,7 +38,8 @@ __global__ __launch_bounds__(kTestWavesPerBlock * 64) void k_test(const BucketDe
                                                          threadIdx.x / 64);
     gss_report *const seg = a.reports + (uint64_t)wave * a.seg_cap;
     const uint32_t seg_cap = a.seg_cap;
-    uint64_t *const dense_out = dense ? a.dense : nullptr;
+    uint64_t *const dense_out = (out & kOutDense) ? a.dense : nullptr;
+    const bool grouped = (out & kOutGrouped) != 0;
     uint32_t produced = 0;  // records of this wavefront (uniform)
     uint32_t bi = 0;
     Counts cnt;  // GSS_TEST_COUNT (uniform)
@@ -49,7 +54,7 @@ __global__ __launch_bounds__(kTestWavesPerBlock * 64) void k_test(const BucketDe
         typename Ts::Tile nxt;
         ts.open(descs, a.n_buckets, bi, tn < a.n_tiles ? tn : last, nxt);  // prefetch, unconditionally
         if constexpr (!WIDE) {
-            produced = ts.run(cur, seg, seg_cap, produced, early_exit, dense_out, cnt);
+            produced = ts.run(cur, seg, seg_cap, produced, early_exit, dense_out, grouped, cnt);
         } else {
             // rows of more than 64 words: the tile is tested chunk by chunk, each
             // chunk's 4096 slots a super-group; with the aggregate pre-test, first
@@ -58,7 +63,7 @@ __global__ __launch_bounds__(kTestWavesPerBlock * 64) void k_test(const BucketDe
             const uint64_t sup = AGG ? ts.super_mask(cur, a.gmask) : a.gmask;
             for (uint32_t g = 0; g < a.G; ++g)
                 if (__ballot((sup >> g) & 1u))
-                    produced = ts.run(cur, seg, seg_cap, produced, early_exit, dense_out, cnt, g, sup);
+                    produced = ts.run(cur, seg, seg_cap, produced, early_exit, dense_out, grouped, cnt, g, sup);
         }
         t = tn;
         cur = nxt;
@@ -78,7 +83,7 @@ __global__ __launch_bounds__(kTestWavesPerBlock * 64) void k_test(const BucketDe
 template <int LPC, int WPL, int MODE, bool HOT, bool AGG>
 __global__ __launch_bounds__(kTestWavesPerBlock * 64) void k_test_list(const BucketDesc *__restrict__ descs,
                                                                         const TestArgs a, uint32_t early_exit,
-                                                                        uint32_t dense) {
+                                                                        uint32_t out) {
     using Ts = Tester<LPC, WPL, MODE, HOT, AGG>;
     extern __shared__ uint64_t lds_rows[];
     __shared__ uint32_t chunk_begin[kMaxBuckets + 1], count[kMaxBuckets];
@@ -98,14 +103,15 @@ __global__ __launch_bounds__(kTestWavesPerBlock * 64) void k_test_list(const Buc
     __syncthreads();
     constexpr uint32_t t_log2 = ilog2<Ts::T>();
     const uint32_t lane = threadIdx.x & 63, j = lane / LPC;
-    __shared__ uint64_t park[kTestWavesPerBlock][Ts::kParkWords];
+    __shared__ __align__(16) uint64_t park[kTestWavesPerBlock][Ts::kParkWords];
     const Ts ts(lane, park[threadIdx.x / 64], a.planes, a.active, a.W, a.hot_rows, lds_rows, 0u, a.agg, a.aggu);
     const uint32_t waves_per_block = blockDim.x / 64;
     const uint32_t n_waves = gridDim.x * waves_per_block;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(xcd_remap(blockIdx.x, gridDim.x) * waves_per_block +
                                                          threadIdx.x / 64);
     gss_report *const seg = a.reports + (uint64_t)wave * a.seg_cap;
-    uint64_t *const dense_out = dense ? a.dense : nullptr;
+    uint64_t *const dense_out = (out & kOutDense) ? a.dense : nullptr;
+    const bool grouped = (out & kOutGrouped) != 0;
     uint32_t produced = 0;
     uint32_t bi = 0;
     Counts cnt;
@@ -118,7 +124,7 @@ __global__ __launch_bounds__(kTestWavesPerBlock * 64) void k_test_list(const Buc
         const uint32_t cn = c + n_waves;
         TileRef nxt = cur;
         if (cn < total) open_listed(descs, a.n_buckets, bi, cn, chunk_begin, count, j, t_log2, nxt);
-        produced = ts.run(cur, seg, a.seg_cap, produced, early_exit, dense_out, cnt);
+        produced = ts.run(cur, seg, a.seg_cap, produced, early_exit, dense_out, grouped, cnt);
         c = cn;
         cur = nxt;
     }
