@@ -309,16 +309,7 @@ BatchFn batch_kernel(uint32_t flags) {
 bool refresh_aggregates(gss_batch &b, uint32_t flags) {
     if (!(flags & GSS_TEST_AGGREGATE)) return false;
     bool moved = false;
-    for (Ctx *c : b.ctxs) {
-        if (!c->agg_valid) {
-            agg_rebuild(*c, 0, 2ull * ((uint64_t)c->cfg.num_vars + 1));
-            c->agg_valid = true;
-        }
-        if ((flags & GSS_TEST_TRIGGER) && !c->aggu_valid) {
-            moved |= c->aggu == nullptr;
-            aggu_rebuild(*c);
-        }
-    }
+    for (Ctx *c : b.ctxs) moved |= agg_refresh(*c, (flags & GSS_TEST_TRIGGER) != 0);
     return moved;
 }
 

@@ -394,7 +394,6 @@ extern "C" gss_status gss_create(const gss_config *cfg, gss_ctx **out) {
         const uint64_t agg_bytes = (uint64_t)c->G * n_rows * agg_elem_bytes(c->RWc);
         c->agg = c->dalloc(agg_bytes);
         launch_fill_u32(*c, (uint32_t *)c->agg, (agg_bytes + 3) / 4, 0);
-        agg_rebuild(*c, 0, 2);
         if (c->G > 1) {
             c->sagg = (uint64_t *)c->dalloc(n_rows * 8);
             launch_fill_u64(*c, c->sagg, n_rows, 0);
@@ -402,6 +401,7 @@ extern "C" gss_status gss_create(const gss_config *cfg, gss_ctx **out) {
         c->active = (uint64_t *)c->dalloc(c->W * sizeof(uint64_t));
         launch_fill_u64(*c, c->active, c->W, 0);
         c->h_active.assign(c->W, 0);
+        agg_init(*c);
 
         // one report segment per wavefront of the widest test launch
         c->max_waves = (uint32_t)c->n_cu * kTestBlocksPerCU * kTestWavesPerBlock;

@@ -177,6 +177,7 @@ struct Ctx {
     bool agg_valid = true;  // false after bulk plane updates: rebuilt by the next aggregate test
     void *aggu = nullptr;   // per variable: bit w set when some active slot of word w has it U
     bool aggu_valid = false;
+    bool agg_used = false;  // a test has asked for the aggregates: deltas keep them valid
     uint64_t *sagg = nullptr;   // G > 1: per row, one bit per super-group (from agg)
     uint64_t *saggu = nullptr;  // G > 1: per variable, one bit per super-group (from aggu)
     bool sagg_valid = false;    // sagg reflects agg
@@ -336,10 +337,11 @@ __device__ inline bool values_invalid(const int8_t *v, uint64_t n, uint64_t tid,
 
 // Bytes of one row's aggregate bits in one chunk: 2 up to 16 words, 4 up to 32, else 8.
 inline uint32_t agg_elem_bytes(uint32_t RWc) { return RWc <= 16 ? 2u : RWc <= 32 ? 4u : 8u; }
-// recomputes the aggregate bits of rows [lo, hi) in every chunk
-void agg_rebuild(Ctx &c, uint64_t lo, uint64_t hi);
-// recomputes the per-variable U bits (trigger-mode aggregates) of every variable
-void aggu_rebuild(Ctx &c);
+// the aggregate bits of variable 0's rows (all others start clear)
+void agg_init(Ctx &c);
+// brings the aggregate bits up to date, and (with_u) the per-variable U bits of the
+// trigger mode; true when the U bits were allocated now
+bool agg_refresh(Ctx &c, bool with_u);
 // G > 1: recomputes the super-group bits from the word bits (sagg, and saggu when
 // the trigger-mode bits are wanted)
 void super_rebuild(Ctx &c, bool with_u);

@@ -17,11 +17,12 @@ namespace gss {
 
 // ---- aggregate bits (Section 4): per row and chunk, bit w = some slot of word
 //      w of the chunk has the row's literal F (element g * n_rows + row).  Packed
-//      word deltas keep them in step; bulk updates (full sets, var-major deltas,
+//      word deltas keep them in step; bulk updates (full sets, large var-major deltas,
 //      cleared slots) mark them stale, and the next aggregate test rebuilds them.
 //      Above them, with more than one chunk, one bit per row and chunk (the
 //      super-group: the aggregate of the chunk's word aggregates), rebuilt from
-//      the word bits before an aggregate test when they changed.
+//      the word bits before an aggregate test when they changed.  Var-major deltas
+//      recompute the listed variables' bits once a test has used them.
 
 __device__ inline uint64_t agg_get(const void *agg, uint32_t RWc, uint64_t i) {
     if (RWc <= 16) return reinterpret_cast<const uint16_t *>(agg)[i];
@@ -38,44 +39,86 @@ __device__ inline void agg_put(void *agg, uint32_t RWc, uint64_t i, uint64_t bit
         reinterpret_cast<uint64_t *>(agg)[i] = bits;
 }
 
-// bit w = word w of chunk g of the row is nonzero
-__device__ inline uint64_t row_nonzero_words(const uint64_t *planes, uint32_t RWc, uint64_t chunk, uint32_t g,
-                                             uint64_t row) {
-    const uint64_t *p = planes + g * chunk + row * RWc;
-    uint64_t bits = 0;
-    for (uint32_t w = 0; w < RWc; ++w) bits |= (uint64_t)(p[w] != 0) << w;
-    return bits;
+// The elements of rows 2 v and 2 v + 1, one after the other, in one store.
+__device__ inline void agg_put2(void *agg, uint32_t RWc, uint64_t i, uint64_t b0, uint64_t b1) {
+    if (RWc <= 16)
+        *reinterpret_cast<uint32_t *>(reinterpret_cast<uint16_t *>(agg) + i) = (uint32_t)b0 | ((uint32_t)b1 << 16);
+    else if (RWc <= 32)
+        *reinterpret_cast<uint2 *>(reinterpret_cast<uint32_t *>(agg) + i) = make_uint2((uint32_t)b0, (uint32_t)b1);
+    else
+        *reinterpret_cast<ulonglong2 *>(reinterpret_cast<uint64_t *>(agg) + i) = make_ulonglong2(b0, b1);
 }
 
-// Thread per (chunk, row) of rows [lo, hi).  Aggregates are stored [G][n_rows].
-__global__ void k_agg_rows(const uint64_t *planes, uint32_t RWc, uint64_t chunk, uint32_t G, uint64_t n_rows, void *agg,
-                           uint64_t lo, uint64_t hi) {
-    const uint64_t span = hi - lo, total = span * G;
-    for (uint64_t x = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; x < total; x += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t g = (uint32_t)(x / span);
-        const uint64_t r = lo + x % span;
-        agg_put(agg, RWc, g * n_rows + r, row_nonzero_words(planes, RWc, chunk, g, r));
+// The aggregates of one chunk of a variable's row pair, a lane per word (RWc lanes a
+// variable): bit w of the results is the ballot of word w.
+struct AggWords {
+    uint64_t f, t, u;  // words with an F slot, with a T slot, with an active U slot
+};
+
+__device__ inline AggWords agg_words(uint64_t f, uint64_t t, uint64_t act, uint32_t RWc, uint32_t lane) {
+    const uint32_t at = lane / RWc * RWc;
+    const uint64_t m = RWc == 64 ? ~0ull : (1ull << RWc) - 1;
+    return AggWords{(__ballot(f != 0) >> at) & m, (__ballot(t != 0) >> at) & m,
+                    (__ballot(((f | t) & act) != act) >> at) & m};
+}
+
+// Aggregates of every variable below n_vars, [G][2 n_vars] and (aggu != null) their U
+// bits [G][n_vars], in one pass over the planes.  A wavefront takes 64 / RWc variables
+// a step, a lane a word of both rows, kAggSteps steps in flight.  Bound by the planes'
+// reads: 25 K variables x 256 words (102 MB) in 18 us and 1 M x 16 words
+// (256 MB) in 38 us with the U bits (a thread a row, its words strided over the lanes:
+// 60 and 490 us for the U bits alone, the rows' own as much again).
+constexpr uint32_t kAggSteps = 8;
+
+__global__ __launch_bounds__(256) void k_agg_rows(const uint64_t *planes, uint32_t RWc, uint64_t chunk, uint64_t n_rows,
+                                                  const uint64_t *active, uint32_t W, void *agg, void *aggu,
+                                                  uint64_t n_vars) {
+    const uint32_t lane = threadIdx.x & 63, g = blockIdx.y, per = 64 / RWc, w = lane % RWc;
+    const uint64_t act = g * RWc + w < W ? active[g * RWc + w] : 0ull;
+    const uint64_t v0 = ((uint64_t)blockIdx.x * 4 + threadIdx.x / 64) * kAggSteps * per + lane / RWc;
+    uint64_t f[kAggSteps], t[kAggSteps];
+#pragma unroll
+    for (uint32_t k = 0; k < kAggSteps; ++k) {  // past the end: the last variable, not stored
+        const uint64_t *p = planes + g * chunk + 2 * min(v0 + k * per, n_vars - 1) * RWc + w;
+        f[k] = p[0];
+        t[k] = p[RWc];
     }
-}
-
-// Trigger-mode aggregate of each variable: bit w = some active slot of word w
-// has the variable U (neither row set there); thread per (chunk, variable),
-// stored [G][n_vars + 1].
-__global__ void k_aggu_rows(const uint64_t *planes, uint32_t RWc, uint64_t chunk, uint32_t G, const uint64_t *active,
-                            uint32_t W, void *aggu, uint64_t n_vars1) {
-    const uint64_t total = n_vars1 * G;
-    for (uint64_t x = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; x < total; x += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t g = (uint32_t)(x / n_vars1);
-        const uint64_t v = x % n_vars1;
-        const uint64_t *pf = planes + g * chunk + (2 * v) * RWc, *pt = pf + RWc;
-        uint64_t bits = 0;
-        for (uint32_t w = 0; w < RWc; ++w) {
-            const uint32_t gw = g * RWc + w;
-            const uint64_t act = gw < W ? active[gw] : 0ull;
-            bits |= (uint64_t)(((pf[w] | pt[w]) & act) != act) << w;
+#pragma unroll
+    for (uint32_t k = 0; k < kAggSteps; ++k) {
+        const uint64_t v = v0 + k * per;
+        const AggWords a = agg_words(f[k], t[k], act, RWc, lane);
+        if (w == 0 && v < n_vars) {
+            agg_put2(agg, RWc, g * n_rows + 2 * v, a.f, a.t);
+            if (aggu) agg_put(aggu, RWc, g * n_vars + v, a.u);
         }
-        agg_put(aggu, RWc, g * n_vars1 + v, bits);
     }
+}
+
+// The same for the listed variables only, after a delta, with their super-group bits
+// (G > 1): the aggregates stay valid at the cost of the delta's rows.
+__global__ __launch_bounds__(256) void k_agg_vars(const uint64_t *planes, uint32_t RWc, uint64_t chunk, uint32_t G,
+                                                  uint64_t n_rows, const uint64_t *active, uint32_t W, void *agg,
+                                                  void *aggu, uint64_t *sagg, uint64_t *saggu, const uint32_t *vars,
+                                                  uint32_t n, const uint32_t *perm) {
+    const uint32_t lane = threadIdx.x & 63, per = 64 / RWc, w = lane % RWc;
+    const uint64_t i = ((uint64_t)blockIdx.x * 4 + threadIdx.x / 64) * per + lane / RWc;
+    const uint64_t v = internal_var(perm, vars[min(i, (uint64_t)n - 1)]);
+    const bool writes = w == 0 && i < n;
+    uint64_t sf = 0, st = 0, su = 0;
+    for (uint32_t g = 0; g < G; ++g) {
+        const uint64_t act = g * RWc + w < W ? active[g * RWc + w] : 0ull;
+        const uint64_t *p = planes + g * chunk + 2 * v * RWc + w;
+        const AggWords a = agg_words(p[0], p[RWc], act, RWc, lane);
+        sf |= (uint64_t)(a.f != 0) << g;
+        st |= (uint64_t)(a.t != 0) << g;
+        su |= (uint64_t)(a.u != 0) << g;
+        if (writes) {
+            agg_put2(agg, RWc, g * n_rows + 2 * v, a.f, a.t);
+            if (aggu) agg_put(aggu, RWc, g * (n_rows / 2) + v, a.u);
+        }
+    }
+    if (writes && sagg) *reinterpret_cast<ulonglong2 *>(sagg + 2 * v) = make_ulonglong2(sf, st);
+    if (writes && saggu) saggu[v] = su;
 }
 
 // Super-group bits (G > 1): bit g of out[i] = the 64-word aggregate in[g][i] is nonzero.
@@ -87,24 +130,52 @@ __global__ void k_super_bits(const uint64_t *in, uint32_t G, uint64_t n, uint64_
     }
 }
 
-void aggu_rebuild(Ctx &c) {
-    const uint64_t n = (uint64_t)c.cfg.num_vars + 1;
-    if (!c.aggu) c.aggu = c.dalloc((uint64_t)c.G * n * agg_elem_bytes(c.RWc));
-    const unsigned grid = (unsigned)std::max<uint64_t>(1, std::min<uint64_t>((n * c.G + 255) / 256, 65536));
-    hipLaunchKernelGGL(k_aggu_rows, dim3(grid), dim3(256), 0, c.stream, c.planes, c.RWc, c.chunk_elems, c.G, c.active,
-                       c.W, c.aggu, n);
+static void launch_agg_rows(Ctx &c, bool with_u, uint64_t n_vars) {
+    const uint64_t per_block = 4ull * kAggSteps * (64 / c.RWc);
+    hipLaunchKernelGGL(k_agg_rows, dim3((unsigned)((n_vars + per_block - 1) / per_block), c.G), dim3(256), 0, c.stream,
+                       c.planes, c.RWc, c.chunk_elems, c.n_rows, c.active, c.W, c.agg, with_u ? c.aggu : nullptr, n_vars);
     GSS_HIP(hipGetLastError());
-    c.aggu_valid = true;
-    c.saggu_valid = false;
 }
 
-void agg_rebuild(Ctx &c, uint64_t lo, uint64_t hi) {
-    if (hi <= lo) return;
-    const unsigned grid = (unsigned)std::max<uint64_t>(1, std::min<uint64_t>(((hi - lo) * c.G + 255) / 256, 65536));
-    hipLaunchKernelGGL(k_agg_rows, dim3(grid), dim3(256), 0, c.stream, c.planes, c.RWc, c.chunk_elems, c.G, c.n_rows,
-                       c.agg, lo, hi);
+void agg_init(Ctx &c) { launch_agg_rows(c, false, 1); }
+
+// Recomputes what is stale of the aggregates, the U bits with them when wanted.
+bool agg_refresh(Ctx &c, bool with_u) {
+    c.agg_used = true;
+    const uint64_t n = (uint64_t)c.cfg.num_vars + 1;
+    bool moved = false;
+    if (with_u && !c.aggu) {
+        c.aggu = c.dalloc((uint64_t)c.G * n * agg_elem_bytes(c.RWc));
+        moved = true;
+    }
+    if (c.agg_valid && (!with_u || c.aggu_valid)) return moved;
+    launch_agg_rows(c, with_u, n);
+    if (!c.agg_valid) c.sagg_valid = false;
+    c.agg_valid = true;
+    if (with_u) {
+        c.aggu_valid = true;
+        c.saggu_valid = false;
+    } else {
+        c.aggu_valid = false;
+    }
+    return moved;
+}
+
+// After a delta of n listed variables (device list): keeps valid aggregates valid when
+// the context uses them, at the cost of the listed rows; a delta of more than half the
+// variables, or aggregates that no test has asked for, are left to the next refresh.
+static void agg_after_delta(Ctx &c, const uint32_t *d_vars, uint32_t n) {
+    if (!c.agg_used || !c.agg_valid || n > c.cfg.num_vars / 2) {
+        c.agg_valid = false;
+        c.aggu_valid = false;
+        return;
+    }
+    const bool with_u = c.aggu_valid, super = c.G > 1 && c.sagg_valid, super_u = with_u && c.G > 1 && c.saggu_valid;
+    const uint32_t per_block = 4 * (64 / c.RWc);
+    hipLaunchKernelGGL(k_agg_vars, dim3((n + per_block - 1) / per_block), dim3(256), 0, c.stream, c.planes, c.RWc,
+                       c.chunk_elems, c.G, c.n_rows, c.active, c.W, c.agg, with_u ? c.aggu : nullptr,
+                       super ? c.sagg : nullptr, super_u ? c.saggu : nullptr, d_vars, n, c.d_perm);
     GSS_HIP(hipGetLastError());
-    c.sagg_valid = false;
 }
 
 void super_rebuild(Ctx &c, bool with_u) {
@@ -296,10 +367,12 @@ __global__ __launch_bounds__(256) void k_set_vars(uint64_t *planes, uint32_t RWc
 // Packed delta: new plane words of listed variables in one 64-slot word.  Thread
 // per variable; f = slots where the variable is F, t = slots where it is T.
 // The variables of one launch are distinct, so each thread owns its two rows'
-// aggregate bits (bit `word` of the word's chunk), updated in place.
+// aggregate bits (bit `word` of the word's chunk), updated in place, and, with aggu
+// != null, its variable's U bit.
 __global__ void k_set_words(uint64_t *planes, uint32_t RWc, uint64_t chunk, uint64_t n_rows, uint32_t word,
                             const uint32_t *vars, const uint64_t *f, const uint64_t *t, uint32_t n, void *agg,
-                            const uint32_t *perm) {
+                            void *aggu, const uint64_t *active, const uint32_t *perm) {
+    const uint64_t act = aggu ? active[word] : 0ull;
     const uint64_t a_base = (uint64_t)(word / kChunkWords) * n_rows;
     const uint64_t bit = 1ull << (word % kChunkWords);
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
@@ -310,6 +383,10 @@ __global__ void k_set_words(uint64_t *planes, uint32_t RWc, uint64_t chunk, uint
         const uint64_t a0 = agg_get(agg, RWc, a_base + row), a1 = agg_get(agg, RWc, a_base + row + 1);
         agg_put(agg, RWc, a_base + row, f[i] ? (a0 | bit) : (a0 & ~bit));
         agg_put(agg, RWc, a_base + row + 1, t[i] ? (a1 | bit) : (a1 & ~bit));
+        if (aggu) {
+            const uint64_t u0 = agg_get(aggu, RWc, (a_base + row) / 2);
+            agg_put(aggu, RWc, (a_base + row) / 2, ((f[i] | t[i]) & act) != act ? (u0 | bit) : (u0 & ~bit));
+        }
     }
 }
 
@@ -329,11 +406,11 @@ __global__ void k_clear_slots(uint64_t *planes, uint32_t RWc, uint64_t chunk, ui
 
 void launch_set_words(Ctx &c, uint32_t word, const uint32_t *vars, const uint64_t *f, const uint64_t *t, uint32_t n) {
     if (n == 0) return;
-    c.aggu_valid = false;
     c.sagg_valid = false;
+    c.saggu_valid = false;
     const unsigned grid = std::max<uint32_t>(1, std::min<uint32_t>((n + 255) / 256, 4096));
     hipLaunchKernelGGL(k_set_words, dim3(grid), dim3(256), 0, c.stream, c.planes, c.RWc, c.chunk_elems, c.n_rows, word,
-                       vars, f, t, n, c.agg, c.d_perm);
+                       vars, f, t, n, c.agg, c.aggu_valid ? c.aggu : nullptr, c.active, c.d_perm);
     GSS_HIP(hipGetLastError());
     c.mutations++;
 }
@@ -526,8 +603,7 @@ extern "C" gss_status gss_set_var_values(gss_ctx *ctx, uint32_t first_slot, uint
         GSS_HIP(hipGetLastError());
     }
     launch_set_vars(c, (const uint32_t *)d, n_vars, dvals, first_slot, n_slots, bad, dev ? c.var_bits : nullptr);
-    c.agg_valid = false;
-    c.aggu_valid = false;
+    agg_after_delta(c, (const uint32_t *)d, n_vars);
     c.stage_done(st);
     if (dev) check_flag(c);  // one synchronisation: device inputs are fully read when the call returns
     GSS_API_END
@@ -568,8 +644,7 @@ extern "C" gss_status gss_set_var_values_async(gss_ctx *ctx, uint32_t first_slot
                        var_blocks, dv, n_vars, c.var_bits, bad);
     GSS_HIP(hipGetLastError());
     launch_set_vars(c, dv, n_vars, values, first_slot, n_slots, bad, c.var_bits);
-    c.agg_valid = false;
-    c.aggu_valid = false;
+    agg_after_delta(c, dv, n_vars);
     c.stage_done(st);
     GSS_API_END
 }

@@ -153,15 +153,9 @@ static Launch prepare(Ctx &c, uint32_t flags) {
     a.aggu = nullptr;
     a.wave_stats = (flags & GSS_TEST_COUNT) ? c.wave_stats : nullptr;
     if (flags & GSS_TEST_AGGREGATE) {
-        if (!c.agg_valid) {
-            agg_rebuild(c, 0, 2ull * ((uint64_t)c.cfg.num_vars + 1));
-            c.agg_valid = true;
-        }
+        agg_refresh(c, (flags & GSS_TEST_TRIGGER) != 0);
         a.agg = c.agg;
-        if (flags & GSS_TEST_TRIGGER) {
-            if (!c.aggu_valid) aggu_rebuild(c);
-            a.aggu = c.aggu;
-        }
+        if (flags & GSS_TEST_TRIGGER) a.aggu = c.aggu;
         if (c.G > 1) {  // the super-group bits above the word bits
             super_rebuild(c, (flags & GSS_TEST_TRIGGER) != 0);
             a.sagg = c.sagg;
