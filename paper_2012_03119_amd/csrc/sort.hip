@@ -3,15 +3,14 @@
 //
 // Ranked (rank_records): a test has at most one record per (clause id, word), so a
 // record's place is the number of records at smaller (id, word) cells.  One pass
-// over the report segments marks the cells (a byte store each: no two records
-// share one, so no atomics), one over the cells packs them into words of 64 bits
-// with their running counts, and one more over the segments stores each record at
-// its place.  The records are read twice and written once, straight from the
-// segments.
+// over the report segments marks the cells (a byte store each: no two records share
+// one, so no atomics; where the records are few among the cells, a bit each), one over
+// the cells takes the running counts of words of 64, and one more over the segments
+// stores each record at its place.  The records are read twice and written once,
+// straight from the segments.
 //
-// Radix (sort_records), where the cells would be many times the records (a large
-// store with few hits) or do not fit the memory budget: a least-significant-digit
-// radix sort written for this library.  The key packs clause id and word ((id << word_bits) | word); each
+// Radix (sort_records), where there are more than 2^31 cells or they do not fit the
+// memory budget: a least-significant-digit radix sort written for this library.  The key packs clause id and word ((id << word_bits) | word); each
 // pass orders the 16-byte records stably by one 8-bit digit of it:
 //
 //   1. per workgroup tile of 4096 records, the count of each digit (LDS);
@@ -194,27 +193,37 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(const gss_report 
 
 constexpr uint32_t kRankBlock = 1u << 16;  // cells per workgroup of the packing kernel (1024 words of 64)
 
-// cells[id << w_log2 | word] = 1 for every kept record; one workgroup per segment.
-// Bound by the segments' reads (8 of each record's 16 bytes are used, but whole
-// lines come in).  Segments grown after a test that lost records hold none yet:
-// what is read there may be no cell, and is left out (here and below).
+// Marks the cell id << w_log2 | word of every kept record; one workgroup per segment.
+// A cell is a byte, stored, or (BITS) a bit, set by an atomic.  Bound by the segments'
+// reads (8 of each record's 16 bytes are used, but whole lines come in), or by the
+// atomics, carried out past the per-XCD caches at about 12 G a second.  Segments grown
+// after a test that lost records hold none yet: what is read there may be no cell,
+// and is left out (here and below).
+template <bool BITS>
 __global__ __launch_bounds__(256) void k_rank_mark(const gss_report *reports, const uint32_t *counts, uint32_t seg_cap,
                                                    uint32_t n_segments, uint32_t w_log2, uint32_t n_cells,
-                                                   uint8_t *cells) {
+                                                   void *cells) {
     for (uint32_t s = blockIdx.x; s < n_segments; s += gridDim.x) {
         const uint32_t n = min(counts[s], seg_cap);
         const gss_report *seg = reports + (uint64_t)s * seg_cap;
         for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
             const uint64_t cell = ((uint64_t)seg[i].clause_id << w_log2) + seg[i].word;
-            if (cell < n_cells) cells[cell] = 1;
+            if (cell >= n_cells) continue;
+            if constexpr (BITS)
+                atomicOr(reinterpret_cast<uint32_t *>(cells) + (cell >> 5), 1u << (cell & 31));
+            else
+                reinterpret_cast<uint8_t *>(cells)[cell] = 1;
         }
     }
 }
 
-// Packs 64 cells a lane into (bits, bits, cells marked before them in the
-// workgroup's 65536, 0), and the workgroup's total.  Four rounds of 256 words; the
-// running count crosses rounds in a register every lane holds.
-__global__ __launch_bounds__(256) void k_rank_pack(const uint4 *cells, uint32_t n_words, uint4 *packed,
+// Counts the marked cells, 64 a lane: the running count before each 64 within the
+// workgroup's 65536, and the workgroup's total.  Byte cells are packed on the way, into
+// (bits, bits, count, 0); bit cells stay as they are, with an array of counts beside
+// them.  Four rounds of 256 words; the running count crosses rounds in a register
+// every lane holds.
+template <bool BITS>
+__global__ __launch_bounds__(256) void k_rank_pack(const void *cells, uint32_t n_words, void *packed,
                                                    uint32_t *totals) {
     __shared__ uint32_t wave_sum[2][4];
     const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -224,13 +233,20 @@ __global__ __launch_bounds__(256) void k_rank_pack(const uint4 *cells, uint32_t 
         const uint32_t w = blockIdx.x * (kRankBlock / 64) + 256 * r + t;
         uint32_t bits[2] = {0, 0};
         if (w < n_words) {
+            if constexpr (BITS) {
+                const uint2 c = reinterpret_cast<const uint2 *>(cells)[w];
+                bits[0] = c.x;
+                bits[1] = c.y;
+            } else {
 #pragma unroll
-            for (uint32_t q = 0; q < 4; ++q) {
-                const uint4 c = cells[(uint64_t)w * 4 + q];
-                const uint32_t u[4] = {c.x, c.y, c.z, c.w};
-                // four cells (bytes 0 or 1) to four bits: byte i lands on bit 28 + i of the product
+                for (uint32_t q = 0; q < 4; ++q) {
+                    const uint4 c = reinterpret_cast<const uint4 *>(cells)[(uint64_t)w * 4 + q];
+                    const uint32_t u[4] = {c.x, c.y, c.z, c.w};
+                    // four cells (bytes 0 or 1) to four bits: byte i lands on bit 28 + i of the product
 #pragma unroll
-                for (uint32_t k = 0; k < 4; ++k) bits[q / 2] |= ((u[k] * 0x10204080u) >> 28) << (16 * (q % 2) + 4 * k);
+                    for (uint32_t k = 0; k < 4; ++k)
+                        bits[q / 2] |= ((u[k] * 0x10204080u) >> 28) << (16 * (q % 2) + 4 * k);
+                }
             }
         }
         const uint32_t mine = __builtin_popcount(bits[0]) + __builtin_popcount(bits[1]);
@@ -248,16 +264,22 @@ __global__ __launch_bounds__(256) void k_rank_pack(const uint4 *cells, uint32_t 
             before += v < wave ? wave_sum[r & 1][v] : 0u;
             run += wave_sum[r & 1][v];
         }
-        if (w < n_words) packed[w] = make_uint4(bits[0], bits[1], before + x - mine, 0u);
+        if (w < n_words) {
+            if constexpr (BITS)
+                reinterpret_cast<uint32_t *>(packed)[w] = before + x - mine;
+            else
+                reinterpret_cast<uint4 *>(packed)[w] = make_uint4(bits[0], bits[1], before + x - mine, 0u);
+        }
     }
     if (t == 0) totals[blockIdx.x] = run;
 }
 
 // Stores every kept record at its place; places at or beyond `limit` are left out.
+template <bool BITS>
 __global__ __launch_bounds__(256) void k_rank_place(const gss_report *reports, const uint32_t *counts, uint32_t seg_cap,
                                                     uint32_t n_segments, uint32_t w_log2, uint32_t n_cells,
-                                                    const uint4 *packed, const uint32_t *base, uint64_t limit,
-                                                    gss_report *out) {
+                                                    const void *cells, const void *packed, const uint32_t *base,
+                                                    uint64_t limit, gss_report *out) {
     for (uint32_t s = blockIdx.x; s < n_segments; s += gridDim.x) {
         const uint32_t n = min(counts[s], seg_cap);
         const uint4 *seg = reinterpret_cast<const uint4 *>(reports) + (uint64_t)s * seg_cap;
@@ -266,7 +288,13 @@ __global__ __launch_bounds__(256) void k_rank_place(const gss_report *reports, c
             const uint64_t at = ((uint64_t)rec.x << w_log2) + rec.y;
             if (at >= n_cells) continue;
             const uint32_t cell = (uint32_t)at;
-            const uint4 p = packed[cell >> 6];
+            uint4 p;  // (bits, bits, count)
+            if constexpr (BITS) {
+                const uint2 c = reinterpret_cast<const uint2 *>(cells)[cell >> 6];
+                p = make_uint4(c.x, c.y, reinterpret_cast<const uint32_t *>(packed)[cell >> 6], 0u);
+            } else {
+                p = reinterpret_cast<const uint4 *>(packed)[cell >> 6];
+            }
             const uint64_t below = (((uint64_t)p.y << 32) | p.x) & ((1ull << (cell & 63)) - 1);
             const uint64_t pos = (uint64_t)base[cell / kRankBlock] + p.z + __builtin_popcountll(below);
             if (pos < limit) reinterpret_cast<uint4 *>(out)[pos] = rec;
@@ -284,47 +312,61 @@ void launch_scan_u32(Ctx &c, uint32_t *x, uint64_t m) {
     GSS_HIP(hipGetLastError());
 }
 
-// Cells of the ranked order: issued ids x words, a power of two of words per id.
-static uint64_t rank_cells(const Ctx &c, uint32_t &w_log2) {
-    w_log2 = 0;
-    while ((1u << w_log2) < c.W) ++w_log2;
-    return ((uint64_t)c.id_loc.size() << w_log2) + 64;
+// The ranked order's plan for the last test's records.  Bit cells cost an atomic a
+// record (2 M took 169 us), byte cells a byte written and one read a cell (96 M took
+// 45 us): bits where a record comes to 240 cells or more.  Then the cells cost little
+// (an eighth of a byte written and read) and so does the workspace, and the radix sort
+// (158 us for 43 K records, 238 us for 815 K) is left for cells beyond 2^31; the
+// kernels index cells by 32 bits.
+struct RankPlan {
+    uint32_t w_log2 = 0;
+    uint64_t cells = 0, words = 0, blocks = 0;
+    size_t marks = 0, packed = 0;  // bytes
+    bool bits = false, fits = false;
+    explicit RankPlan(const Ctx &c) {
+        while ((1u << w_log2) < c.W) ++w_log2;  // a power of two of words per issued id
+        cells = ((uint64_t)c.id_loc.size() << w_log2) + 64;
+        words = (cells + 63) / 64;
+        blocks = (cells + kRankBlock - 1) / kRankBlock;
+        bits = c.n_kept < cells / 240;
+        marks = (words * (bits ? 8 : 64) + 255) / 256 * 256;
+        packed = (words * (bits ? 4 : 16) + 255) / 256 * 256;
+        fits = cells <= (1ull << 31);
+    }
+};
+
+// Bytes of the ranked order's workspace, or 0 where the radix sort is used.
+uint64_t rank_bytes(const Ctx &c) {
+    const RankPlan p(c);
+    return p.fits ? p.marks + p.packed + (p.blocks * 4 + 255) / 256 * 256 : 0;
 }
 
-// Bytes of the ranked order's workspace for the last test's records, or 0 where the
-// radix sort is used.  Ranking costs its cells (cleared and read once: 82 us for 96 M
-// cells with 815 K records, 53 us for 64 M with 103 K) and about 25 ns per thousand
-// records; the radix sort costs 158 us for 43 K records, 238 us for 815 K.  So ranking
-// wins up to about 160 M cells plus 128 a record.  The kernels index cells by 32 bits.
-uint64_t rank_bytes(const Ctx &c) {
-    uint32_t w_log2;
-    const uint64_t cells = rank_cells(c, w_log2);
-    if (cells >= (1ull << 32) || cells > (160ull << 20) + 128 * c.n_kept) return 0;
-    const uint64_t words = (cells + 63) / 64, blocks = (cells + kRankBlock - 1) / kRankBlock;
-    return words * 64 + words * 16 + (blocks * 4 + 255) / 256 * 256;
+template <bool BITS>
+static void launch_rank(Ctx &c, const RankPlan &p, char *ws, gss_report *dst, uint64_t limit) {
+    void *marks = ws, *packed = ws + p.marks;
+    uint32_t *totals = (uint32_t *)(ws + p.marks + p.packed);
+    launch_fill_u64(c, (uint64_t *)marks, p.marks / 8, 0);
+    const dim3 grid(std::max<uint32_t>(1, std::min<uint32_t>(c.last_waves, 65535)));
+    hipLaunchKernelGGL(k_rank_mark<BITS>, grid, dim3(256), 0, c.stream, c.reports, c.seg_counts, c.seg_cap, c.last_waves,
+                       p.w_log2, (uint32_t)p.cells, marks);
+    GSS_HIP(hipGetLastError());
+    hipLaunchKernelGGL(k_rank_pack<BITS>, dim3((unsigned)p.blocks), dim3(256), 0, c.stream, marks, (uint32_t)p.words,
+                       packed, totals);
+    GSS_HIP(hipGetLastError());
+    launch_scan_u32(c, totals, p.blocks);
+    hipLaunchKernelGGL(k_rank_place<BITS>, grid, dim3(256), 0, c.stream, c.reports, c.seg_counts, c.seg_cap, c.last_waves,
+                       p.w_log2, (uint32_t)p.cells, marks, packed, totals, limit, dst);
+    GSS_HIP(hipGetLastError());
 }
 
 // Queues the ranked order of the last test's kept records, the first `limit` of it,
 // into dst (device); ws: rank_bytes of device memory, 256-byte aligned.
 void rank_records(Ctx &c, char *ws, gss_report *dst, uint64_t limit) {
-    uint32_t w_log2;
-    const uint64_t cells = rank_cells(c, w_log2);
-    const uint64_t words = (cells + 63) / 64, blocks = (cells + kRankBlock - 1) / kRankBlock;
-    uint8_t *flags = (uint8_t *)ws;
-    uint4 *packed = (uint4 *)(ws + words * 64);
-    uint32_t *totals = (uint32_t *)(ws + words * 64 + words * 16);
-    launch_fill_u64(c, (uint64_t *)flags, words * 8, 0);
-    const dim3 grid(std::max<uint32_t>(1, std::min<uint32_t>(c.last_waves, 65535)));
-    hipLaunchKernelGGL(k_rank_mark, grid, dim3(256), 0, c.stream, c.reports, c.seg_counts, c.seg_cap, c.last_waves,
-                       w_log2, (uint32_t)cells, flags);
-    GSS_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_rank_pack, dim3((unsigned)blocks), dim3(256), 0, c.stream, (const uint4 *)flags,
-                       (uint32_t)words, packed, totals);
-    GSS_HIP(hipGetLastError());
-    launch_scan_u32(c, totals, blocks);
-    hipLaunchKernelGGL(k_rank_place, grid, dim3(256), 0, c.stream, c.reports, c.seg_counts, c.seg_cap, c.last_waves,
-                       w_log2, (uint32_t)cells, packed, totals, limit, dst);
-    GSS_HIP(hipGetLastError());
+    const RankPlan p(c);
+    if (p.bits)
+        launch_rank<true>(c, p, ws, dst, limit);
+    else
+        launch_rank<false>(c, p, ws, dst, limit);
 }
 
 void sort_records(Ctx &c, gss_report *src, uint64_t n, gss_report *dst) {
