@@ -200,6 +200,7 @@ void *Ctx::host_stage(size_t bytes) {
         hstage_bytes = 0;
         size_t want = bytes < (1u << 20) ? (1u << 20) : bytes;
         GSS_HIP(hipHostMalloc(&hstage, want, hipHostMallocDefault));
+        GSS_HIP(hipHostGetDevicePointer(&hdstage, hstage, 0));
         hstage_bytes = want;
     }
     return hstage;

@@ -241,6 +241,7 @@ struct Ctx {
     void *dstage = nullptr;
     size_t dstage_bytes = 0;
     void *hstage = nullptr;
+    void *hdstage = nullptr;  // hstage as kernels address it
     size_t hstage_bytes = 0;
 
     hipEvent_t ev_start = nullptr, ev_stop = nullptr;
@@ -377,6 +378,7 @@ void sort_records(Ctx &c, gss_report *src, uint64_t n, gss_report *dst);  // src
 // The same order straight from the report segments, by ranking (id, word) cells:
 // workspace bytes (0: use sort_records) and the queued launches.
 uint64_t rank_bytes(const Ctx &c);
+bool rank_is_small(const Ctx &c);  // one launch, which may write pinned host memory
 void rank_records(Ctx &c, char *ws, gss_report *dst, uint64_t limit);
 void launch_scan_u32(Ctx &c, uint32_t *x, uint64_t m);  // in place, exclusive, on c.stream
 uint32_t *deferred_flag(Ctx &c);

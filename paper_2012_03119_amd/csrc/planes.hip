@@ -476,10 +476,12 @@ __global__ void k_check_vars(const uint32_t *vars, uint32_t n, uint32_t *bits, u
 }
 
 // Both checks of a queued delta in one launch: the first var_blocks workgroups
-// take the variable list (already on the device), marking repeats (bit 2 of
-// *bad); the others check the truth values (bit 1).
+// take the variable list, marking repeats (bit 2 of *bad); the others check the truth
+// values (bit 1).  The list is already on the device, or (list != null) read here
+// from pinned host memory and stored to vars.
 __global__ __launch_bounds__(256) void k_check_delta(const int8_t *vals, uint64_t n_vals, uint32_t var_blocks,
-                                                     const uint32_t *vars, uint32_t n, uint32_t *bits, uint32_t *bad) {
+                                                     const uint32_t *list, uint32_t *vars, uint32_t n, uint32_t *bits,
+                                                     uint32_t *bad) {
     if (blockIdx.x >= var_blocks) {
         const uint32_t b = blockIdx.x - var_blocks, value_blocks = gridDim.x - var_blocks;
         if (values_invalid(vals, n_vals, b * (uint64_t)blockDim.x + threadIdx.x, (uint64_t)value_blocks * blockDim.x))
@@ -488,7 +490,8 @@ __global__ __launch_bounds__(256) void k_check_delta(const int8_t *vals, uint64_
     }
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const uint32_t v = vars[i], m = 1u << (v & 31);
+    const uint32_t v = list ? list[i] : vars[i], m = 1u << (v & 31);
+    if (list) vars[i] = v;
     if (atomicOr(&bits[v >> 5], m) & m) atomicOr(bad, 2u);
 }
 
@@ -510,6 +513,12 @@ static void check_delta_slots(const Ctx &c, uint32_t first_slot, uint32_t n_slot
         GSS_REQUIRE((c.h_active[w] & sm) == sm, GSS_ERR_INVALID_ARG, "slot range includes inactive slots");
     }
 }
+
+// Uploads up to these sizes are read by their kernels from the pinned ring slot, with
+// no copy queued before them: a variable list of a queued delta; a host delta's list
+// and values, or a packed delta, each byte read once (a kernel reads pinned memory at
+// 44 GB/s, as fast as a copy).
+constexpr size_t kDirectList = 64u << 10, kDirectDelta = 1u << 20;
 
 static void check_values_host(const int8_t *v, uint64_t n) {
     uint8_t bad = 0;
@@ -591,11 +600,12 @@ extern "C" gss_status gss_set_var_values(gss_ctx *ctx, uint32_t first_slot, uint
 
     const size_t vars_bytes = ((size_t)n_vars * 4 + 255) / 256 * 256;
     const size_t bytes = vars_bytes + (dev ? 0 : nv);
-    const Ctx::Staged st = c.stage_upload(bytes);
-    char *h = st.h, *d = st.d;
+    const bool direct = !dev && bytes <= kDirectList;
+    const Ctx::Staged st = c.stage_upload(bytes, direct);
+    char *h = st.h, *d = direct ? const_cast<char *>(st.hd) : st.d;
     std::memcpy(h, vars, (size_t)n_vars * 4);
     if (!dev) std::memcpy(h + vars_bytes, values, nv);
-    GSS_HIP(hipMemcpyAsync(d, h, bytes, hipMemcpyHostToDevice, c.stream));
+    if (!direct) GSS_HIP(hipMemcpyAsync(d, h, bytes, hipMemcpyHostToDevice, c.stream));
     const int8_t *dvals = dev ? values : (const int8_t *)(d + vars_bytes);
     if (dev) {
         hipLaunchKernelGGL(k_check_vars, dim3((n_vars + 255) / 256), dim3(256), 0, c.stream, (const uint32_t *)d, n_vars,
@@ -623,25 +633,31 @@ extern "C" gss_status gss_set_var_values_async(gss_ctx *ctx, uint32_t first_slot
         c.var_bits = (uint32_t *)c.dalloc(((uint64_t)c.cfg.num_vars / 32 + 1) * 4);
         launch_fill_u32(c, c.var_bits, (uint64_t)c.cfg.num_vars / 32 + 1, 0);
     }
-    // the list goes up through a pinned ring slot on the copy stream, which runs
-    // while the test ahead of it executes (on the context stream, a copy would
-    // start only when that test ends); the checking kernel waits for it
-    if (!c.copy_stream) {
-        GSS_HIP(hipStreamCreateWithFlags(&c.copy_stream, hipStreamNonBlocking));
-        GSS_HIP(hipEventCreateWithFlags(&c.ev_copy, hipEventDisableTiming));
-    }
+    // A short list is read from its pinned ring slot by the checking kernel.  A longer
+    // one goes up on the copy stream, which runs while the test ahead of it executes
+    // (on the context stream, a copy would start only when that test ends); the
+    // checking kernel waits for it.  The copy's three calls take about 20 us of host
+    // time, and its wait leaves the stream idle for 5 us; 64 KiB over the bus take the
+    // kernel 2 us.
     const size_t bytes = (size_t)n_vars * 4;
+    const bool direct = bytes <= kDirectList;
     const Ctx::Staged st = c.stage_upload(bytes);
     std::memcpy(st.h, vars, bytes);
     uint32_t *dv = (uint32_t *)st.d;
-    GSS_HIP(hipMemcpyAsync(dv, st.h, bytes, hipMemcpyHostToDevice, c.copy_stream));
-    GSS_HIP(hipEventRecord(c.ev_copy, c.copy_stream));
-    GSS_HIP(hipStreamWaitEvent(c.stream, c.ev_copy, 0));
+    if (!direct) {
+        if (!c.copy_stream) {
+            GSS_HIP(hipStreamCreateWithFlags(&c.copy_stream, hipStreamNonBlocking));
+            GSS_HIP(hipEventCreateWithFlags(&c.ev_copy, hipEventDisableTiming));
+        }
+        GSS_HIP(hipMemcpyAsync(dv, st.h, bytes, hipMemcpyHostToDevice, c.copy_stream));
+        GSS_HIP(hipEventRecord(c.ev_copy, c.copy_stream));
+        GSS_HIP(hipStreamWaitEvent(c.stream, c.ev_copy, 0));
+    }
     uint32_t *bad = deferred_flag(c);  // sticky: set by this check or an earlier one not yet reported
     const uint64_t nv = (uint64_t)n_vars * n_slots;
     const uint32_t var_blocks = (n_vars + 255) / 256;
     hipLaunchKernelGGL(k_check_delta, dim3(var_blocks + fill_grid((nv + 15) / 16)), dim3(256), 0, c.stream, values, nv,
-                       var_blocks, dv, n_vars, c.var_bits, bad);
+                       var_blocks, direct ? (const uint32_t *)st.hd : nullptr, dv, n_vars, c.var_bits, bad);
     GSS_HIP(hipGetLastError());
     launch_set_vars(c, dv, n_vars, values, first_slot, n_slots, bad, c.var_bits);
     agg_after_delta(c, dv, n_vars);
@@ -682,12 +698,13 @@ extern "C" gss_status gss_update_words(gss_ctx *ctx, uint32_t word, uint32_t n_v
     for (uint32_t i = 0; i < n_vars; ++i)
         GSS_REQUIRE((f_words[i] & t_words[i]) == 0, GSS_ERR_INVALID_ARG, "a slot cannot be both F and T");
     const size_t vb = ((size_t)n_vars * 4 + 255) / 256 * 256, wb = ((size_t)n_vars * 8 + 255) / 256 * 256;
-    const Ctx::Staged st = c.stage_upload(vb + 2 * wb);
-    char *h = st.h, *d = st.d;
+    const bool direct = vb + 2 * wb <= kDirectDelta;
+    const Ctx::Staged st = c.stage_upload(vb + 2 * wb, direct);
+    char *h = st.h, *d = direct ? const_cast<char *>(st.hd) : st.d;
     std::memcpy(h, vars, (size_t)n_vars * 4);
     std::memcpy(h + vb, f_words, (size_t)n_vars * 8);
     std::memcpy(h + vb + wb, t_words, (size_t)n_vars * 8);
-    GSS_HIP(hipMemcpyAsync(d, h, vb + 2 * wb, hipMemcpyHostToDevice, c.stream));
+    if (!direct) GSS_HIP(hipMemcpyAsync(d, h, vb + 2 * wb, hipMemcpyHostToDevice, c.stream));
     launch_set_words(c, word, (const uint32_t *)d, (const uint64_t *)(d + vb), (const uint64_t *)(d + vb + wb), n_vars);
     c.stage_done(st);
     GSS_API_END

@@ -254,9 +254,14 @@ static void complete(Ctx &c) {
     c.release_deferred();
     c.stats.kernel_launches++;
     if (!c.timed) return;
-    GSS_HIP(hipEventSynchronize(c.ev_stop));  // recorded before the finalize kernel: already complete
-    float ms = 0.f;
-    GSS_HIP(hipEventElapsedTime(&ms, c.ev_start, c.ev_stop));
+    float ms = 0.f;  // both events were recorded before the finalize kernel: complete
+    hipError_t e = hipEventElapsedTime(&ms, c.ev_start, c.ev_stop);
+    if (e == hipErrorNotReady) {
+        (void)hipGetLastError();
+        GSS_HIP(hipEventSynchronize(c.ev_stop));
+        e = hipEventElapsedTime(&ms, c.ev_start, c.ev_stop);
+    }
+    GSS_HIP(e);
     c.stats.last_kernel_ms = ms;
     c.stats.total_kernel_ms += ms;
     c.stats.timed_launches++;
@@ -368,6 +373,9 @@ static uint64_t end_test(Ctx &c, uint32_t flags, bool launched) {
     return n;
 }
 
+// Records of a host fetch that its kernel writes into pinned memory (256 KiB).
+constexpr uint64_t kDirectRecords = 1u << 14;
+
 static void queue_stitch(Ctx &c, const Segments &sg, gss_report *dst, uint64_t n) {
     if (!n) return;
     const unsigned grid = std::max<uint32_t>(1, std::min<uint32_t>(c.last_waves, 65535));
@@ -388,13 +396,14 @@ void queue_stitch(Ctx &c, gss_report *dst, uint64_t n) { queue_stitch(c, context
 static void fetch_sorted(Ctx &c, gss_report *dst, uint64_t n, bool dev, char *ws, uint64_t rank) {
     if (rank) {
         char *own = nullptr;
-        if (!ws) {
+        const bool small = rank_is_small(c);  // its cells are in LDS
+        if (!ws && !small) {
             try {
                 ws = own = (char *)c.dalloc(rank);
             } catch (const Error &) {  // no room: the radix sort needs less where the cells outnumber the records
             }
         }
-        if (ws) {
+        if (ws || small) {
             try {
                 rank_records(c, ws, dst, n);
                 if (own) c.sync();
@@ -506,6 +515,20 @@ extern "C" gss_status gss_fetch_reports(gss_ctx *ctx, gss_report *out, uint64_t 
     if (n) {
         GSS_REQUIRE(out != nullptr, GSS_ERR_INVALID_ARG, "null argument");
         const bool dev = is_device_pointer(out);
+        // A small list for the host is written straight into pinned memory by the
+        // kernel that makes it and copied from there: a queued copy into the caller's
+        // pageable memory took about 30 us.
+        if (!dev && n <= kDirectRecords && (!(c.last_flags & GSS_TEST_SORTED) || rank_is_small(c))) {
+            gss_report *h = (gss_report *)c.host_stage(n * sizeof(gss_report));
+            if (c.last_flags & GSS_TEST_SORTED)
+                rank_records(c, nullptr, (gss_report *)c.hdstage, n);
+            else
+                queue_stitch(c, (gss_report *)c.hdstage, n);
+            c.sync();
+            std::memcpy(out, h, n * sizeof(gss_report));
+            *out_n = n;
+            return GSS_OK;
+        }
         // host records pass through the bulk staging; a small ordered fetch has its
         // workspace behind them there
         const uint64_t rank = (c.last_flags & GSS_TEST_SORTED) ? rank_bytes(c) : 0;

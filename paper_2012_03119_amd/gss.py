@@ -662,7 +662,8 @@ class Context:
         import torch
         if any(isinstance(x, torch.Tensor) and x.is_cuda for x in xs):
             cur = torch.cuda.current_stream()
-            if cur != self.torch_stream:  # on the same stream the order already holds
+            # on the same stream the order already holds; a stream with nothing left to do holds nothing up
+            if cur != self.torch_stream and not cur.query():
                 self.torch_stream.wait_stream(cur)
 
     # -- ABI calls

@@ -13,8 +13,9 @@ from paper_2012_03119_amd import gen, gss
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n,slots", [(3, 64), (63, 64), (65_535, 64), (65_600, 64), (21_846, 192), (1_000, 4_160)])
+@pytest.mark.parametrize("n,slots", [(3, 64), (63, 64), (9_000, 64), (65_535, 64), (65_600, 64), (21_846, 192), (1_000, 4_160)])
 def test_ranked_order(n, slots):
+    import torch
     print(f"ranked order {n} clauses {slots} slots", flush=True)
     rng = np.random.default_rng(n + slots)
     V = 400
@@ -37,6 +38,9 @@ def test_ranked_order(n, slots):
         assert ctx.test(gss.GSS_TEST_SORTED) == len(want)
         assert (ctx.fetch_reports(len(want)) == want).all()
         assert (ctx.fetch_reports(max(1, len(want) // 2)) == want[: max(1, len(want) // 2)]).all()
+        dev = torch.zeros((len(want), 2), dtype=torch.int64, device="cuda")
+        assert gss.gss_fetch_reports_into(ctx.ctx, dev.data_ptr(), len(want)) == len(want)
+        assert (dev.cpu().numpy().view(want.dtype).reshape(-1) == want).all()
 
 
 def _sparse_problem(n, n_slots, max_slots):
