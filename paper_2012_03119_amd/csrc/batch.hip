@@ -406,6 +406,7 @@ bool complete_batch(gss_batch &b, uint32_t flags, bool &any_overflow_growable) {
         c.release_deferred();
         const unsigned long long *sum = b.h_summary + 4 * s;
         c.last_waves = b.grid * kTestWavesPerBlock;
+        c.offsets_ready = true;  // k_finalize_batch wrote them
         c.n_reports = sum[0];
         c.n_kept = sum[2];
         c.tested = true;

@@ -310,6 +310,7 @@ static void destroy_ctx(Ctx *c) {
     c->dfree(c->seg_counts);
     c->dfree(c->seg_offsets);
     c->dfree(c->d_summary);
+    c->dfree(c->arrived);
     c->dfree(c->dense);
     c->dfree(c->dstage);
     if (c->hstage) (void)hipHostFree(c->hstage);
@@ -412,6 +413,8 @@ extern "C" gss_status gss_create(const gss_config *cfg, gss_ctx **out) {
         c->seg_counts = (uint32_t *)c->dalloc((uint64_t)c->max_waves * 4);
         c->seg_offsets = (uint64_t *)c->dalloc(((uint64_t)c->max_waves + 1) * 8);
         c->d_summary = (unsigned long long *)c->dalloc(4 * sizeof(unsigned long long));
+        c->arrived = (unsigned long long *)c->dalloc((1 + kArriveGroups) * kArriveStride * 8);
+        launch_fill_u64(*c, (uint64_t *)c->arrived, (1 + kArriveGroups) * kArriveStride, 0);
         GSS_HIP(hipHostMalloc(&c->h_summary, 8 * sizeof(unsigned long long), hipHostMallocDefault));
         std::memset(c->h_summary, 0, 8 * sizeof(unsigned long long));
         GSS_HIP(hipHostGetDevicePointer((void **)&c->hd_summary, c->h_summary, 0));
@@ -454,6 +457,8 @@ extern "C" const char *gss_last_error(const gss_ctx *ctx) {
 extern "C" gss_status gss_get_stats(const gss_ctx *ctx, gss_stats *out) {
     const Ctx *c = reinterpret_cast<const Ctx *>(ctx);
     if (!c || !out) return GSS_ERR_INVALID_ARG;
+    // the last test's events are read on demand
+    if (read_timing(*const_cast<Ctx *>(c)) != hipSuccess) return GSS_ERR_DEVICE;
     *out = c->stats;
     out->live_clauses = c->live;
     out->device_bytes = c->device_bytes;
@@ -467,6 +472,7 @@ extern "C" gss_status gss_reset_stats(gss_ctx *ctx) {
     Ctx *c = reinterpret_cast<Ctx *>(ctx);
     if (!c) return GSS_ERR_INVALID_ARG;
     c->stats = gss_stats{};
+    c->timing_pending = false;
     return GSS_OK;
 }
 

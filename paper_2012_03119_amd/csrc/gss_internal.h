@@ -77,6 +77,8 @@ constexpr uint32_t kTestBlocksPerCU = 8;
 constexpr uint32_t kMinSegment = 16;   // smallest report segment per wavefront (grown on demand)
 constexpr uint64_t kScratchBytes = 64ull << 20;  // gss_test_noalloc's segments, per GPU
 constexpr int kMaxDevices = 64;
+// arrival words of a test's workgroups: a root and this many groups, a line apart
+constexpr uint32_t kArriveGroups = 32, kArriveStride = 32;  // words of 8 bytes
 
 // length class: smallest c >= kMinClass with 2^c >= len
 inline int length_class(uint32_t len) {
@@ -109,7 +111,6 @@ struct BucketDesc {
 };
 
 struct TestArgs {
-    BucketDesc b[kMaxBuckets];
     uint32_t n_buckets;
     uint32_t n_tiles;
     const uint64_t *planes;   // [G][2 * (num_vars + 1)][RWc], RWc = min(RW, 64), RW = lanes per clause >= W
@@ -130,6 +131,11 @@ struct TestArgs {
     uint64_t n_rows;          // rows of the plane table (the stride of the aggregate chunks)
     uint64_t gmask;           // super-groups holding an active slot (bit g: words 64g .. 64g + 63)
     uint32_t *wave_stats;     // GSS_TEST_COUNT: [n_waves][2] gathers, pre-test settled words; null: not counted
+    // kOutSummary: the last workgroup to end writes the summary to the host
+    unsigned long long *arrived;       // root and group words, zero between launches (see finish_test)
+    const uint32_t *deferred;          // verdict of the asynchronous updates before the test
+    unsigned long long *host_summary;  // pinned: {records, 1 = a segment overflowed, records, verdict, serial}
+    unsigned long long serial;
 };
 
 // ---------------------------------------------------------------------------
@@ -199,6 +205,8 @@ struct Ctx {
     uint32_t last_waves = 0;                 // wavefronts of the last launch
     uint32_t *seg_counts = nullptr;          // [max_waves]
     uint64_t *seg_offsets = nullptr;         // [max_waves + 1] exclusive prefix of the kept records
+    bool offsets_ready = false;              // seg_offsets holds the last test's
+    unsigned long long *arrived = nullptr;   // workgroups of the running test that have ended, with their records
     unsigned long long *d_summary = nullptr;  // device {total, max, kept, deferred verdict}
     unsigned long long *h_summary = nullptr;  // pinned host copy, written by the finalize kernel
     unsigned long long *hd_summary = nullptr; // h_summary as kernels address it
@@ -246,6 +254,7 @@ struct Ctx {
 
     hipEvent_t ev_start = nullptr, ev_stop = nullptr;
     bool timed = false;  // the last launched test kernel has timing events
+    bool timing_pending = false;  // a completed test's events are not read yet (read_timing)
     hipEvent_t ev_stage = nullptr;  // recorded after the last queued use of the staging buffers
     // queued deltas: their variable lists go up on a copy stream of their own while
     // the test ahead of them runs (created by the first gss_set_var_values_async)
@@ -361,6 +370,7 @@ void copy_in(Ctx &c, void *dst, const void *src_hd, size_t bytes);
 // Queues the copy of the last test's first n kept records, as one list, into
 // device memory dst (on the context's stream).
 void queue_stitch(Ctx &c, gss_report *dst, uint64_t n);
+hipError_t read_timing(Ctx &c) noexcept;  // the kernel time of a timed test into the statistics
 void scratch_setup(int device);  // once per device, from gss_create
 // Activity (learned priority enabled): state for ids below n_ids (validate
 // before an insert changes anything); bump the clauses with a record in the

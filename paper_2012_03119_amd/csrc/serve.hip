@@ -285,6 +285,7 @@ void gss_server::run() {
     bool pending = false;
     uint64_t run_id = 0;
     double del_due = 0.0, last = now();
+    (void)read_timing(C);
     const double kernel_ms0 = C.stats.total_kernel_ms;
     const char *phase = "start";  // what the manager was doing (named in an error)
     auto timed = [&](double &acc, auto &&fn) {
@@ -779,6 +780,7 @@ void gss_server::run() {
         if (roff[k]) (void)hipHostFree(roff[k]);
     }
     C.dfree(route_dev);
+    (void)read_timing(C);
     res.gpu_ms = C.stats.total_kernel_ms - kernel_ms0;
 }
 

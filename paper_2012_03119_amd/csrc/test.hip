@@ -196,33 +196,63 @@ struct Segments {
 
 static Segments context_segments(Ctx &c) { return Segments{c.reports, c.seg_counts, c.seg_offsets, c.seg_cap}; }
 
-// Queues the test kernel and the finalize kernel, which writes the summary and
-// the test's serial into pinned host memory.
-static void launch(Ctx &c, const Launch &L, uint32_t flags, const Segments &sg) {
+// Adds the kernel time of the last timed test to the statistics.  Its events are read
+// when the statistics are asked for, or before they are recorded again: reading them
+// as the test completes held the caller up for the second event, behind the kernel.
+hipError_t read_timing(Ctx &c) noexcept {
+    if (!c.timing_pending) return hipSuccess;
+    c.timing_pending = false;
+    float ms = 0.f;
+    hipError_t e = hipEventSynchronize(c.ev_stop);
+    if (e == hipSuccess) e = hipEventElapsedTime(&ms, c.ev_start, c.ev_stop);
+    if (e != hipSuccess) return e;
+    c.stats.last_kernel_ms = ms;
+    c.stats.total_kernel_ms += ms;
+    c.stats.timed_launches++;
+    return hipSuccess;
+}
+
+// Queues the finalize kernel of the last test: its summary, its segments' offsets and
+// its serial, the latter also into pinned host memory.
+static void queue_finalize(Ctx &c, const Segments &sg, uint32_t n_waves, uint64_t serial) {
+    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, c.stream, sg.counts, n_waves, sg.cap, sg.offsets,
+                       c.d_summary, deferred_flag(c), c.hd_summary, (unsigned long long)serial);
+    GSS_HIP(hipGetLastError());
+}
+
+// Queues the test kernel, which writes the summary and the test's serial into pinned
+// host memory (`summary`), or has the finalize kernel do so behind it.
+static void launch(Ctx &c, Launch &L, uint32_t flags, const Segments &sg, bool summary) {
     const uint64_t serial = c.tests_launched + 1;
     // timing events around the kernel on every timing_interval-th launch (each
     // event leaves the stream idle for a few microseconds; attaching them to the
     // dispatch instead, with hipExtLaunchKernel, measured slower: 24 against 10 us
     // of host time per launch, on the path between two tests)
     c.timed = serial % std::max<uint32_t>(1u, c.cfg.timing_interval) == 0;
+    if (c.timed) GSS_HIP(read_timing(c));
     if (c.timed) GSS_HIP(hipEventRecord(c.ev_start, c.stream));
     // records that will be ordered, or whose clauses' hits will be counted, come grouped
     const bool grouped = (flags & GSS_TEST_SORTED) || c.prio;
+    summary = summary && L.grid < kMaxSummaryBlocks;
+    L.args.arrived = c.arrived;
+    L.args.deferred = deferred_flag(c);
+    L.args.host_summary = c.hd_summary;
+    L.args.serial = serial;
     hipLaunchKernelGGL(L.fn, dim3(L.grid), dim3(kTestWavesPerBlock * 64), L.lds, c.stream, L.descs, L.args,
                        (flags & GSS_TEST_NO_EARLY_EXIT) ? 0u : 1u,
-                       ((flags & GSS_TEST_DENSE) ? kOutDense : 0u) | (grouped ? kOutGrouped : 0u));
+                       ((flags & GSS_TEST_DENSE) ? kOutDense : 0u) | (grouped ? kOutGrouped : 0u) |
+                           (summary ? kOutSummary : 0u));
     GSS_HIP(hipGetLastError());
     if (c.timed) GSS_HIP(hipEventRecord(c.ev_stop, c.stream));
     const uint32_t n_waves = L.grid * kTestWavesPerBlock;
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, c.stream, sg.counts, n_waves, sg.cap, sg.offsets,
-                       c.d_summary, deferred_flag(c), c.hd_summary, (unsigned long long)serial);
-    GSS_HIP(hipGetLastError());
+    if (!summary) queue_finalize(c, sg, n_waves, serial);
+    c.offsets_ready = !summary;
     c.tests_launched = serial;
     c.last_waves = n_waves;
     c.launch_mutations = c.mutations;
 }
 
-// True once the last launched test's finalize kernel has written its serial to
+// True once the last launched test (or its finalize kernel) has written its serial to
 // the host; a device error on the stream is raised.
 static bool summary_arrived(Ctx &c, bool check_stream) {
     const volatile unsigned long long *hs = c.h_summary;
@@ -243,7 +273,7 @@ static bool summary_arrived(Ctx &c, bool check_stream) {
     return false;
 }
 
-// Waits for a launched test and records its kernel time.  The wait polls the
+// Waits for a launched test.  The wait polls the
 // serial in pinned memory rather than blocking in the runtime: the caller is
 // about to queue the next test, and a blocked thread wakes too late to keep the
 // device busy.  The stream is queried now and then for device errors.
@@ -253,18 +283,17 @@ static void complete(Ctx &c) {
     c.tests_completed = c.tests_launched;
     c.release_deferred();
     c.stats.kernel_launches++;
-    if (!c.timed) return;
-    float ms = 0.f;  // both events were recorded before the finalize kernel: complete
-    hipError_t e = hipEventElapsedTime(&ms, c.ev_start, c.ev_stop);
-    if (e == hipErrorNotReady) {
-        (void)hipGetLastError();
-        GSS_HIP(hipEventSynchronize(c.ev_stop));
-        e = hipEventElapsedTime(&ms, c.ev_start, c.ev_stop);
-    }
-    GSS_HIP(e);
-    c.stats.last_kernel_ms = ms;
-    c.stats.total_kernel_ms += ms;
-    c.stats.timed_launches++;
+    if (c.timed) c.timing_pending = true;
+}
+
+// The same, and after an overflow that the test kernel reported itself, the exact
+// counts of its segments from the finalize kernel.
+static void complete_with_overflow(Ctx &c) {
+    complete(c);
+    if (c.offsets_ready || !c.h_summary[1]) return;
+    queue_finalize(c, context_segments(c), c.last_waves, c.tests_launched);
+    c.sync();
+    c.offsets_ready = true;
 }
 
 // Checks flags and prepares a test; returns false when there is nothing to launch.
@@ -304,7 +333,7 @@ static bool begin_test(Ctx &c, uint32_t flags, Launch &L) {
         c.last_waves = 0;
         return false;
     }
-    launch(c, L, flags, context_segments(c));
+    launch(c, L, flags, context_segments(c), true);
     return true;
 }
 
@@ -314,7 +343,7 @@ static bool begin_test(Ctx &c, uint32_t flags, Launch &L) {
 static uint64_t end_test(Ctx &c, uint32_t flags, bool launched) {
     uint64_t n = 0, kept = 0;
     if (launched) {
-        complete(c);
+        complete_with_overflow(c);
         n = c.h_summary[0];
         kept = c.h_summary[2];
         const uint64_t largest = c.h_summary[1];
@@ -336,8 +365,8 @@ static uint64_t end_test(Ctx &c, uint32_t flags, bool launched) {
             if (grown && c.mutations == c.launch_mutations) {
                 c.stats.regrows++;
                 Launch L = prepare(c, flags);
-                launch(c, L, flags, context_segments(c));
-                complete(c);
+                launch(c, L, flags, context_segments(c), true);
+                complete_with_overflow(c);
                 n = c.h_summary[0];
                 kept = c.h_summary[2];
             }
@@ -384,7 +413,15 @@ static void queue_stitch(Ctx &c, const Segments &sg, gss_report *dst, uint64_t n
     GSS_HIP(hipGetLastError());
 }
 
-void queue_stitch(Ctx &c, gss_report *dst, uint64_t n) { queue_stitch(c, context_segments(c), dst, n); }
+void queue_stitch(Ctx &c, gss_report *dst, uint64_t n) {
+    if (n && !c.offsets_ready) {
+        hipLaunchKernelGGL(k_offsets, dim3(1), dim3(1024), 0, c.stream, c.seg_counts, c.last_waves, c.seg_cap,
+                           c.seg_offsets, c.d_summary);
+        GSS_HIP(hipGetLastError());
+        c.offsets_ready = true;
+    }
+    queue_stitch(c, context_segments(c), dst, n);
+}
 
 // The first n of the ordered records into dst (device memory; the caller's when
 // dev).  Ranked from the segments when its workspace (`rank` bytes, at ws or
@@ -669,7 +706,7 @@ extern "C" gss_status gss_test_noalloc(gss_ctx *ctx, uint32_t flags, gss_report 
         // the context's records of an earlier test are not touched; they are no
         // longer the last test's
         c.tested = false;
-        launch(c, L, flags, sg);
+        launch(c, L, flags, sg, false);  // the stitch below needs the offsets
         complete(c);
         n = c.h_summary[0];
         kept = c.h_summary[2];
