@@ -82,9 +82,7 @@ constexpr uint32_t kArriveGroups = 32, kArriveStride = 32;  // words of 8 bytes
 
 // length class: smallest c >= kMinClass with 2^c >= len
 inline int length_class(uint32_t len) {
-    int c = kMinClass;
-    while ((1u << c) < len) ++c;
-    return c;
+    return len <= (1u << kMinClass) ? kMinClass : 32 - __builtin_clz(len - 1);
 }
 
 // ---------------------------------------------------------------------------
@@ -190,6 +188,7 @@ struct Ctx {
     bool saggu_valid = false;   // saggu reflects aggu
     uint64_t *active = nullptr;
     std::vector<uint64_t> h_active;
+    std::vector<uint64_t> id_seen;   // scratch bitmap for removals (kept all-zero)
     std::vector<uint64_t> var_seen;  // scratch bitmap for argument checks (kept all-zero)
     uint32_t *var_bits = nullptr;    // device twin of var_seen for device-input checks (kept all-zero)
 

@@ -438,9 +438,13 @@ static void upload_active(Ctx &c) {
     c.stage_done(st);
 }
 
-// Range and distinctness of a variable list, O(n) with a bitmap that is cleared
-// again afterwards.
+// Range and distinctness of a variable list: an increasing one (as a solver's trail
+// sorted, or a run of variables) by its neighbours, any other in O(n) with a bitmap
+// that is cleared again afterwards.
 static void check_vars(Ctx &c, const uint32_t *vars, uint32_t n_vars) {
+    uint32_t unordered = vars[0] < 1 || vars[n_vars - 1] > c.cfg.num_vars;
+    for (uint32_t i = 1; i < n_vars; ++i) unordered |= vars[i] <= vars[i - 1];
+    if (!unordered) return;
     std::vector<uint64_t> &seen = c.var_seen;
     if (seen.size() < (uint64_t)c.cfg.num_vars / 64 + 1) seen.assign((uint64_t)c.cfg.num_vars / 64 + 1, 0);
     uint32_t bad = 0;  // 1: out of range, 2: repeated
@@ -695,8 +699,9 @@ extern "C" gss_status gss_update_words(gss_ctx *ctx, uint32_t word, uint32_t n_v
     GSS_REQUIRE(vars && f_words && t_words, GSS_ERR_INVALID_ARG, "null argument");
     GSS_REQUIRE(word < c.W, GSS_ERR_CAPACITY, "word beyond max_slots / 64");
     check_vars(c, vars, n_vars);
-    for (uint32_t i = 0; i < n_vars; ++i)
-        GSS_REQUIRE((f_words[i] & t_words[i]) == 0, GSS_ERR_INVALID_ARG, "a slot cannot be both F and T");
+    uint64_t both = 0;
+    for (uint32_t i = 0; i < n_vars; ++i) both |= f_words[i] & t_words[i];
+    GSS_REQUIRE(both == 0, GSS_ERR_INVALID_ARG, "a slot cannot be both F and T");
     const size_t vb = ((size_t)n_vars * 4 + 255) / 256 * 256, wb = ((size_t)n_vars * 8 + 255) / 256 * 256;
     const bool direct = vb + 2 * wb <= kDirectDelta;
     const Ctx::Staged st = c.stage_upload(vb + 2 * wb, direct);
