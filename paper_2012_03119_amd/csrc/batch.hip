@@ -68,8 +68,8 @@ __device__ inline void locate(const SchedSeg *segs, uint32_t n_segs, uint32_t g,
 // Each wavefront walks the global tiles g = wave, wave + N, ... and, like the
 // single-store kernel, opens the next tile (its store located, its metadata and
 // first codes in flight) while it tests the current one.
-// The falsified kernel fits 5 wavefronts per SIMD in 96 registers without
-// spilling (4 unconstrained); the others would spill, and keep their own count.
+// The falsified kernel fits 5 wavefronts per SIMD in 96 registers and 28 bytes of
+// scratch (4 unconstrained); the others would spill more, and keep their own count.
 template <int MODE, bool AGG>
 __global__ __launch_bounds__(kTestWavesPerBlock * 64)
 __attribute__((amdgpu_waves_per_eu(MODE == 0 && !AGG ? 5 : 1))) void k_test_batch(const StoreDesc *__restrict__ stores,

@@ -68,7 +68,7 @@ template <int LPC, int WPL, int MODE, bool HOT, bool AGG, bool WIDE = false>
 __global__ __launch_bounds__(kTestWavesPerBlock * 64) void k_test(const BucketDesc *__restrict__ descs,
                                                                    const TestArgs a, uint32_t early_exit,
                                                                    uint32_t out) {
-    using Ts = Tester<LPC, WPL, MODE, HOT, AGG, WIDE>;
+    using Ts = Tester<LPC, WPL, MODE, HOT, AGG, WIDE, join_rows<LPC, MODE, WIDE>>;
     extern __shared__ uint64_t lds_rows[];
     if constexpr (HOT) {
         const uint32_t n = a.hot_rows * Ts::RW;
@@ -133,7 +133,7 @@ template <int LPC, int WPL, int MODE, bool HOT, bool AGG>
 __global__ __launch_bounds__(kTestWavesPerBlock * 64) void k_test_list(const BucketDesc *__restrict__ descs,
                                                                         const TestArgs a, uint32_t early_exit,
                                                                         uint32_t out) {
-    using Ts = Tester<LPC, WPL, MODE, HOT, AGG>;
+    using Ts = Tester<LPC, WPL, MODE, HOT, AGG, false, HOT ? 1 : join_rows<LPC, MODE, false>>;  // HOT: 82 registers with two
     extern __shared__ uint64_t lds_rows[];
     __shared__ uint32_t chunk_begin[kMaxBuckets + 1], count[kMaxBuckets];
     if (threadIdx.x == 0) {

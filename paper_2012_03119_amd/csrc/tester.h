@@ -172,9 +172,20 @@ __device__ inline Words<WPL> load_words(const char *p) {
     return r;
 }
 
+// A join is a chain of dependent loads (code, row), so two steps' rows go out
+// together where that costs no wavefront per SIMD: k_test in us, one -> two steps,
+// 1 M clauses x 256 slots 116 -> 104, x 2048 277 -> 262, 2 M x 4096 557 -> 551, 200 K
+// x 1024 46 -> 41.  One step in trigger mode (its step has two rows already), with 2
+// lanes per clause (86 registers, 5 wavefronts: 700 K x 448 103 -> 106), in rows of
+// several chunks (85), and in the batched kernel, which would spill (342 -> 393).
+// Three steps leave 5 wavefronts nearly everywhere: 300 K x 1024, rows new each pass, 51 -> 55.
+template <int LPC, int MODE, bool WIDE>
+constexpr uint32_t join_rows = (MODE == 0 && LPC != 2 && !WIDE) ? 2 : 1;
+
 // One store's clause test for one lane: LPC lanes per clause, WPL words per lane,
-// a plane row of RW = LPC * WPL words.  MODE 0 = falsified, 1 = trigger.
-template <int LPC, int WPL, int MODE, bool HOT, bool AGG = false, bool WIDE = false>
+// a plane row of RW = LPC * WPL words.  MODE 0 = falsified, 1 = trigger.  ROWS:
+// steps of the join in flight together (join_rows).
+template <int LPC, int WPL, int MODE, bool HOT, bool AGG = false, bool WIDE = false, uint32_t ROWS = 1>
 struct Tester {
     static constexpr uint32_t kGroup = kGroupOf<AGG>;
     static constexpr uint32_t T = 64 / LPC;                 // clauses per wavefront (and per tile)
@@ -358,7 +369,10 @@ struct Tester {
                 p = min(p, n - 1);
                 return __builtin_amdgcn_raw_buffer_load_b32(cur.lits, off + (p >> 2) * (T * 16u) + (p & 3u) * 4u, 0, 0);
             };
-            uint32_t code = code_at(k + j);
+            constexpr uint32_t kRows = ROWS;  // steps whose rows are in flight together
+            uint32_t code[kRows];
+#pragma unroll
+            for (uint32_t u = 0; u < kRows; ++u) code[u] = code_at(k + u * T + j);
             // the first step's product tells the chance survivors, which end there
             for (uint32_t p0 = k, stop = k + T;; stop = n) {
                 uint64_t a[WPL], o[WPL];
@@ -367,21 +381,34 @@ struct Tester {
                     a[i] = ~0ull;
                     o[i] = 0;
                 }
-                for (; p0 < min(stop, n); p0 += T) {
-                    const uint32_t next = code_at(p0 + T + j);  // in flight during this step's rows
-                    const bool reads = ((mine >> sub) & 1u) && p0 + j < n;
-                    if (cnt.on) cnt.gathers += (uint32_t)__builtin_popcountll(__ballot(reads));
-                    if (reads) {
-                        const Words<WPL> f = gather(pb, code);
-                        if constexpr (MODE == 1) {
-                            const Words<WPL> t = gather(pb, code ^ 1u);
+                while (p0 < min(stop, n)) {
+                    const uint32_t end = min(stop, n), steps = stop < n ? 1u : kRows;
+                    uint32_t next[kRows];  // codes in flight during this step's rows
 #pragma unroll
-                            for (int i = 0; i < WPL; ++i) o[i] = (a[i] & ~(f.v[i] | t.v[i])) | (o[i] & f.v[i]);
+                    for (uint32_t u = 0; u < kRows; ++u) next[u] = code_at(p0 + (steps + u) * T + j);
+                    const bool wanted = (mine >> sub) & 1u;
+                    if (cnt.on) {
+#pragma unroll
+                        for (uint32_t u = 0; u < kRows; ++u)
+                            cnt.gathers += (uint32_t)__builtin_popcountll(__ballot(wanted && p0 + u * T + j < end));
+                    }
+                    if (wanted && p0 + j < end) {
+                        Words<WPL> f[kRows];
+#pragma unroll
+                        for (uint32_t u = 0; u < kRows; ++u) f[u] = gather(pb, p0 + u * T + j < end ? code[u] : 0u);
+                        if constexpr (MODE == 1) {
+                            const Words<WPL> t = gather(pb, code[0] ^ 1u);
+#pragma unroll
+                            for (int i = 0; i < WPL; ++i) o[i] = (a[i] & ~(f[0].v[i] | t.v[i])) | (o[i] & f[0].v[i]);
                         }
 #pragma unroll
-                        for (int i = 0; i < WPL; ++i) a[i] &= f.v[i];
+                        for (uint32_t u = 0; u < kRows; ++u)
+#pragma unroll
+                            for (int i = 0; i < WPL; ++i) a[i] &= f[u].v[i];
                     }
-                    code = next;
+#pragma unroll
+                    for (uint32_t u = 0; u < kRows; ++u) code[u] = next[u];
+                    p0 += steps * T;
                 }
 #pragma unroll
                 for (uint32_t d = LPC; d < 64; d <<= 1) {
