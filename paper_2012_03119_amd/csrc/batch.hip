@@ -51,7 +51,7 @@ __device__ uint32_t batch_run(const StoreDesc &st, const TileRef &cur, gss_repor
     using Ts = Tester<LPC, WPL, MODE, false, AGG>;
     const Ts ts(threadIdx.x & 63, park, st.planes, st.active, st.W, 0, nullptr, 0u, st.agg, st.aggu);
     Counts none;
-    return ts.run(cur, seg, st.seg_cap, produced, early_exit, nullptr, false, none);
+    return ts.run(cur, seg, st.seg_cap, produced, early_exit, nullptr, false, nullptr, none);
 }
 
 // The store and store-local tile of global tile g: segs[lo].begin <= g < segs[lo + 1].begin.
@@ -411,6 +411,7 @@ bool complete_batch(gss_batch &b, uint32_t flags, bool &any_overflow_growable) {
         c.n_kept = sum[2];
         c.tested = true;
         c.last_flags = flags & ~GSS_TEST_GRAPH;
+        c.hits_valid = false;
         c.stats.tests_run++;
         c.stats.last_reports = sum[0];
         act = 0;

@@ -123,9 +123,18 @@ bool is_device_pointer(const void *p) {
 
 bool Ctx::fits(uint64_t bytes) {
     if (cfg.hbm_budget_bytes == 0 || device_bytes + bytes <= cfg.hbm_budget_bytes) return true;
-    if (deferred_frees.empty()) return false;
+    if (deferred_frees.empty() && !hits) return false;
     sync();  // releases the deferred frees
+    if (device_bytes + bytes > cfg.hbm_budget_bytes) release_hits();
     return device_bytes + bytes <= cfg.hbm_budget_bytes;
+}
+
+// Gives up the hit words (an ordered fetch marks the records again); the stream is idle.
+void Ctx::release_hits() {
+    dfree(hits);
+    hits = nullptr;
+    hits_bytes = 0;
+    hits_armed = hits_valid = false;
 }
 
 void *Ctx::dalloc(size_t bytes) {
@@ -142,8 +151,9 @@ void *Ctx::dalloc(size_t bytes) {
             (void)hipGetLastError();
             p = nullptr;
         }
-        if (p || attempt == 1 || deferred_frees.empty()) break;
+        if (p || attempt == 1 || (deferred_frees.empty() && !hits)) break;
         sync();  // out of device memory with frees pending: release them and retry once
+        release_hits();
     }
     GSS_REQUIRE(p != nullptr, cfg.dev_alloc ? GSS_ERR_DEVICE : GSS_ERR_CAPACITY,
                 "device allocation of " + std::to_string(bytes) + " bytes failed");
@@ -312,6 +322,7 @@ static void destroy_ctx(Ctx *c) {
     c->dfree(c->d_summary);
     c->dfree(c->arrived);
     c->dfree(c->dense);
+    c->dfree(c->hits);
     c->dfree(c->dstage);
     if (c->hstage) (void)hipHostFree(c->hstage);
     for (auto &s : c->ring) {

@@ -121,6 +121,7 @@ struct TestArgs {
     uint32_t *seg_counts;     // [n_waves]: records produced by each wavefront (beyond seg_cap: counted only)
     uint32_t seg_cap;
     uint64_t *dense;          // GSS_TEST_DENSE: [n_ids][W]
+    void *hits;               // grouped records: per id the RWc bits of its words with a record; null: not kept
     uint32_t sched_run;       // schedule: a low-priority clause is tested when (sched_run + id) % 4 == 0
     const void *agg;          // aggregate bits per row (element of 2, 4 or 8 bytes by RWc; [G][rows]); null: no pre-test
     const void *aggu;         // trigger mode: per variable, bit w = word w has an active slot where it is U ([G][vars])
@@ -243,6 +244,15 @@ struct Ctx {
     uint64_t *dense = nullptr;
     uint64_t dense_rows = 0;
     uint64_t dense_ids = 0;  // ids issued when the last dense test ran: the rows it wrote
+
+    // Bit w of entry id (RWc bits): clause id has a record in word w, written by a test
+    // whose records will be ordered.  Given up whenever memory is short.
+    void *hits = nullptr;
+    size_t hits_bytes = 0;
+    uint64_t hits_ids = 0;    // entries the last such test cleared
+    bool hits_armed = false;  // the test in flight, or the last one, writes them
+    bool hits_valid = false;  // they are the last test's, and no record was lost
+    void release_hits();
 
     // staging for uploads (device) and pinned host staging
     void *dstage = nullptr;
@@ -387,6 +397,7 @@ void sort_records(Ctx &c, gss_report *src, uint64_t n, gss_report *dst);  // src
 // The same order straight from the report segments, by ranking (id, word) cells:
 // workspace bytes (0: use sort_records) and the queued launches.
 uint64_t rank_bytes(const Ctx &c);
+bool rank_uses_hits(uint64_t bytes);       // whether hit words of that size are ranked (and not too small or large)
 bool rank_is_small(const Ctx &c);  // one launch, which may write pinned host memory
 void rank_records(Ctx &c, char *ws, gss_report *dst, uint64_t limit);
 void launch_scan_u32(Ctx &c, uint32_t *x, uint64_t m);  // in place, exclusive, on c.stream

@@ -193,7 +193,8 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(const gss_report 
 
 constexpr uint32_t kRankBlock = 1u << 16;  // cells per workgroup of the packing kernel (1024 words of 64)
 
-// Marks the cell id << w_log2 | word of every kept record; one workgroup per segment.
+// Marks the cell id << w_log2 | word of every kept record, where the test kept no hit
+// words (rows under 8 words or over 64, the aggregate pre-test); one workgroup per segment.
 // A cell is a byte, stored, or (BITS) a bit, set by an atomic.  Bound by the segments'
 // reads (8 of each record's 16 bytes are used, but whole lines come in), or by the
 // atomics, carried out past the per-XCD caches at about 12 G a second.  Segments grown
@@ -274,7 +275,46 @@ __global__ __launch_bounds__(256) void k_rank_pack(const void *cells, uint32_t n
     if (t == 0) totals[blockIdx.x] = run;
 }
 
+// Places R records a thread: records i0, i0 + blockDim, ... of a segment of n.
+template <bool BITS, uint32_t R>
+__device__ inline void rank_place(const uint4 *seg, uint32_t i0, uint32_t n, uint32_t w_log2, uint32_t n_cells,
+                                  const void *cells, const void *packed, const uint32_t *base, uint64_t limit,
+                                  gss_report *out) {
+    uint4 rec[R], p[R];  // p: (bits, bits, count)
+    uint32_t cell[R], first[R];
+    bool ok[R];
+#pragma unroll
+    for (uint32_t r = 0; r < R; ++r) {
+        const uint32_t i = i0 + r * blockDim.x;
+        rec[r] = seg[i < n ? i : i0];
+    }
+#pragma unroll
+    for (uint32_t r = 0; r < R; ++r) {
+        const uint64_t at = ((uint64_t)rec[r].x << w_log2) + rec[r].y;
+        ok[r] = at < n_cells && i0 + r * blockDim.x < n;
+        cell[r] = ok[r] ? (uint32_t)at : 0u;
+        if constexpr (BITS) {
+            const uint2 c = reinterpret_cast<const uint2 *>(cells)[cell[r] >> 6];
+            p[r] = make_uint4(c.x, c.y, reinterpret_cast<const uint32_t *>(packed)[cell[r] >> 6], 0u);
+        } else {
+            p[r] = reinterpret_cast<const uint4 *>(packed)[cell[r] >> 6];
+        }
+        first[r] = base[cell[r] / kRankBlock];
+    }
+#pragma unroll
+    for (uint32_t r = 0; r < R; ++r) {
+        const uint64_t below = (((uint64_t)p[r].y << 32) | p[r].x) & ((1ull << (cell[r] & 63)) - 1);
+        const uint64_t pos = (uint64_t)first[r] + p[r].z + __builtin_popcountll(below);
+        if (ok[r] && pos < limit) reinterpret_cast<uint4 *>(out)[pos] = rec[r];
+    }
+}
+
 // Stores every kept record at its place; places at or beyond `limit` are left out.
+// Bound by memory: the records' lines in and out (10.1 M records, 0.32 GB: 115 us, 2.8
+// TB/s), reached through a chain of three loads.  A thread of a segment that gives all
+// threads one has four records in flight: with one 126 us, two 120, eight 107, but 0.4 M
+// records in short segments took 22 us with four and 27 with eight.  Non-temporal
+// stores: 154.
 template <bool BITS>
 __global__ __launch_bounds__(256) void k_rank_place(const gss_report *reports, const uint32_t *counts, uint32_t seg_cap,
                                                     uint32_t n_segments, uint32_t w_log2, uint32_t n_cells,
@@ -283,21 +323,12 @@ __global__ __launch_bounds__(256) void k_rank_place(const gss_report *reports, c
     for (uint32_t s = blockIdx.x; s < n_segments; s += gridDim.x) {
         const uint32_t n = min(counts[s], seg_cap);
         const uint4 *seg = reinterpret_cast<const uint4 *>(reports) + (uint64_t)s * seg_cap;
-        for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
-            const uint4 rec = seg[i];
-            const uint64_t at = ((uint64_t)rec.x << w_log2) + rec.y;
-            if (at >= n_cells) continue;
-            const uint32_t cell = (uint32_t)at;
-            uint4 p;  // (bits, bits, count)
-            if constexpr (BITS) {
-                const uint2 c = reinterpret_cast<const uint2 *>(cells)[cell >> 6];
-                p = make_uint4(c.x, c.y, reinterpret_cast<const uint32_t *>(packed)[cell >> 6], 0u);
-            } else {
-                p = reinterpret_cast<const uint4 *>(packed)[cell >> 6];
-            }
-            const uint64_t below = (((uint64_t)p.y << 32) | p.x) & ((1ull << (cell & 63)) - 1);
-            const uint64_t pos = (uint64_t)base[cell / kRankBlock] + p.z + __builtin_popcountll(below);
-            if (pos < limit) reinterpret_cast<uint4 *>(out)[pos] = rec;
+        uint32_t i = threadIdx.x;
+        if (n > blockDim.x) {
+            for (; i < n; i += 4 * blockDim.x)
+                rank_place<BITS, 4>(seg, i, n, w_log2, n_cells, cells, packed, base, limit, out);
+        } else if (i < n) {
+            rank_place<BITS, 1>(seg, i, n, w_log2, n_cells, cells, packed, base, limit, out);
         }
     }
 }
@@ -376,7 +407,8 @@ void launch_scan_u32(Ctx &c, uint32_t *x, uint64_t m) {
     GSS_HIP(hipGetLastError());
 }
 
-// The ranked order's plan for the last test's records.  Bit cells cost an atomic a
+// The ranked order's plan for the last test's records: from the test's hit words where
+// it kept them (bit cells, already marked).  Otherwise bit cells cost an atomic a
 // record (2 M took 169 us), byte cells a byte written and one read a cell (96 M took
 // 45 us): bits where a record comes to 240 cells or more.  Then the cells cost little
 // (an eighth of a byte written and read) and so does the workspace, and the radix sort
@@ -386,19 +418,29 @@ struct RankPlan {
     uint32_t w_log2 = 0;
     uint64_t cells = 0, words = 0, blocks = 0;
     size_t marks = 0, packed = 0;  // bytes
-    bool bits = false, fits = false, small = false;
+    bool hits = false, bits = false, fits = false, small = false;
     explicit RankPlan(const Ctx &c) {
         while ((1u << w_log2) < c.W) ++w_log2;  // a power of two of words per issued id
         cells = ((uint64_t)c.id_loc.size() << w_log2) + 64;
         words = (cells + 63) / 64;
         blocks = (cells + kRankBlock - 1) / kRankBlock;
-        bits = c.n_kept < cells / 240;
-        marks = (words * (bits ? 8 : 64) + 255) / 256 * 256;
+        small = cells <= kSmallCells && c.n_kept <= kSmallRecords;
+        hits = c.hits_valid && !small;
+        if (hits) {  // the test's own bit cells
+            w_log2 = 0;
+            while ((1u << w_log2) < c.RWc) ++w_log2;
+            words = (c.hits_ids * c.RWc + 511) / 512 * 8;
+            cells = words * 64;
+            blocks = (cells + kRankBlock - 1) / kRankBlock;
+        }
+        bits = hits || c.n_kept < cells / 240;
+        marks = hits ? 0 : (words * (bits ? 8 : 64) + 255) / 256 * 256;
         packed = (words * (bits ? 4 : 16) + 255) / 256 * 256;
         fits = cells <= (1ull << 31);
-        small = cells <= kSmallCells && c.n_kept <= kSmallRecords;
     }
 };
+
+bool rank_uses_hits(uint64_t bytes) { return bytes * 8 > kSmallCells && bytes * 8 <= (1ull << 31); }
 
 bool rank_is_small(const Ctx &c) { return RankPlan(c).small; }
 
@@ -411,13 +453,15 @@ uint64_t rank_bytes(const Ctx &c) {
 
 template <bool BITS>
 static void launch_rank(Ctx &c, const RankPlan &p, char *ws, gss_report *dst, uint64_t limit) {
-    void *marks = ws, *packed = ws + p.marks;
+    void *marks = p.hits ? c.hits : ws, *packed = ws + p.marks;
     uint32_t *totals = (uint32_t *)(ws + p.marks + p.packed);
-    launch_fill_u64(c, (uint64_t *)marks, p.marks / 8, 0);
     const dim3 grid(std::max<uint32_t>(1, std::min<uint32_t>(c.last_waves, 65535)));
-    hipLaunchKernelGGL(k_rank_mark<BITS>, grid, dim3(256), 0, c.stream, c.reports, c.seg_counts, c.seg_cap, c.last_waves,
-                       p.w_log2, (uint32_t)p.cells, marks);
-    GSS_HIP(hipGetLastError());
+    if (!p.hits) {
+        launch_fill_u64(c, (uint64_t *)marks, p.marks / 8, 0);
+        hipLaunchKernelGGL(k_rank_mark<BITS>, grid, dim3(256), 0, c.stream, c.reports, c.seg_counts, c.seg_cap,
+                           c.last_waves, p.w_log2, (uint32_t)p.cells, marks);
+        GSS_HIP(hipGetLastError());
+    }
     hipLaunchKernelGGL(k_rank_pack<BITS>, dim3((unsigned)p.blocks), dim3(256), 0, c.stream, marks, (uint32_t)p.words,
                        packed, totals);
     GSS_HIP(hipGetLastError());

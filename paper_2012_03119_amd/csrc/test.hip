@@ -149,6 +149,7 @@ static Launch prepare(Ctx &c, uint32_t flags) {
     a.seg_counts = c.seg_counts;
     a.seg_cap = c.seg_cap;
     a.dense = c.dense;
+    a.hits = nullptr;
     a.agg = nullptr;
     a.aggu = nullptr;
     a.wave_stats = (flags & GSS_TEST_COUNT) ? c.wave_stats : nullptr;
@@ -296,6 +297,33 @@ static void complete_with_overflow(Ctx &c) {
     c.offsets_ready = true;
 }
 
+// Clears the hit words for a test whose records will be ordered, and gives them to its
+// kernel: the ordered fetch then has its marks without reading the records for them.
+// The words cost the test 1% and the records' marks took a third of the ordered fetch.
+// Not where a clause's bits are less than a byte of its own, in rows of several chunks,
+// with the aggregate pre-test (few records, and not grouped), or for a table that
+// one workgroup orders; without the memory for them the fetch marks the records.
+static void arm_hits(Ctx &c, uint32_t flags, Launch &L) {
+    c.hits_armed = c.hits_valid = false;
+    if (!(flags & GSS_TEST_SORTED) || L.args.agg || c.G > 1 || c.RWc < 8) return;
+    const uint64_t bytes = (c.id_loc.size() * c.RWc / 8 + 63) / 64 * 64;
+    if (!rank_uses_hits(bytes)) return;
+    if (bytes > c.hits_bytes) {
+        const uint64_t want = std::max<uint64_t>(bytes, c.hits_bytes + c.hits_bytes / 2);
+        c.release_hits();
+        try {
+            c.hits = c.dalloc(want);
+        } catch (const Error &) {
+            return;
+        }
+        c.hits_bytes = want;
+    }
+    launch_fill_u64(c, (uint64_t *)c.hits, bytes / 8, 0);
+    c.hits_ids = c.id_loc.size();
+    c.hits_armed = true;
+    L.args.hits = c.hits;
+}
+
 // Checks flags and prepares a test; returns false when there is nothing to launch.
 static bool begin_test(Ctx &c, uint32_t flags, Launch &L) {
     const uint32_t known = GSS_TEST_TRIGGER | GSS_TEST_NO_EARLY_EXIT | GSS_TEST_SORTED | GSS_TEST_DENSE |
@@ -332,10 +360,12 @@ static bool begin_test(Ctx &c, uint32_t flags, Launch &L) {
     c.stats.last_literals = lits;
     c.tested = false;
     L = prepare(c, flags);
+    c.hits_armed = c.hits_valid = false;
     if (L.args.n_tiles == 0) {
         c.last_waves = 0;
         return false;
     }
+    arm_hits(c, flags, L);
     launch(c, L, flags, context_segments(c), true);
     return true;
 }
@@ -368,6 +398,7 @@ static uint64_t end_test(Ctx &c, uint32_t flags, bool launched) {
             if (grown && c.mutations == c.launch_mutations) {
                 c.stats.regrows++;
                 Launch L = prepare(c, flags);
+                if (c.hits_armed) L.args.hits = c.hits;  // the same bits again
                 launch(c, L, flags, context_segments(c), true);
                 complete_with_overflow(c);
                 n = c.h_summary[0];
@@ -395,6 +426,7 @@ static uint64_t end_test(Ctx &c, uint32_t flags, bool launched) {
     if (flags & GSS_TEST_DENSE) n = kept = 0;
     c.n_reports = n;
     c.n_kept = kept;
+    c.hits_valid = launched && c.hits_armed && kept == n;
     c.stats.last_reports = n;
     // a failed asynchronous update is reported here; the test itself ran on the
     // state without it, and its records stay available
@@ -430,16 +462,22 @@ void queue_stitch(Ctx &c, gss_report *dst, uint64_t n) {
 // dev).  Ranked from the segments when its workspace (`rank` bytes, at ws or
 // allocated here) is to be had; otherwise every kept record is stitched and
 // radix-sorted, and the first n copied.  With 10.1 M records of 4 M clauses x 16 words
-// the ranked order's kernels take 0.25 ms (mark 61 us, pack 15, place 157, clearing
-// 12), where the radix sort took 5.9 ms; the pass of delta, test and ordered fetch went
-// from 6.53 to 1.02 ms.
+// the ranked order's kernels take 0.13 ms from the test's hit words (place 115 us, pack
+// 5, clearing 3; without them mark 62, pack 15, place 111, clearing 12), where the
+// radix sort took 5.9 ms.
 static void fetch_sorted(Ctx &c, gss_report *dst, uint64_t n, bool dev, char *ws, uint64_t rank) {
     if (rank) {
         char *own = nullptr;
         const bool small = rank_is_small(c);  // its cells are in LDS
+        if (rank_bytes(c) > rank) ws = nullptr;  // the hit words went to make room for ws
         if (!ws && !small) {
             try {
+                rank = rank_bytes(c);
                 ws = own = (char *)c.dalloc(rank);
+                if (rank_bytes(c) > rank) {
+                    c.dfree(own);
+                    ws = own = nullptr;
+                }
             } catch (const Error &) {  // no room: the radix sort needs less where the cells outnumber the records
             }
         }

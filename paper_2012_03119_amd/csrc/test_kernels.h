@@ -102,7 +102,7 @@ __global__ __launch_bounds__(kTestWavesPerBlock * 64) void k_test(const BucketDe
         typename Ts::Tile nxt;
         ts.open(descs, a.n_buckets, bi, tn < a.n_tiles ? tn : last, nxt);  // prefetch, unconditionally
         if constexpr (!WIDE) {
-            produced = ts.run(cur, seg, seg_cap, produced, early_exit, dense_out, grouped, cnt);
+            produced = ts.run(cur, seg, seg_cap, produced, early_exit, dense_out, grouped, a.hits, cnt);
         } else {
             // rows of more than 64 words: the tile is tested chunk by chunk, each
             // chunk's 4096 slots a super-group; with the aggregate pre-test, first
@@ -111,7 +111,7 @@ __global__ __launch_bounds__(kTestWavesPerBlock * 64) void k_test(const BucketDe
             const uint64_t sup = AGG ? ts.super_mask(cur, a.gmask) : a.gmask;
             for (uint32_t g = 0; g < a.G; ++g)
                 if (__ballot((sup >> g) & 1u))
-                    produced = ts.run(cur, seg, seg_cap, produced, early_exit, dense_out, grouped, cnt, g, sup);
+                    produced = ts.run(cur, seg, seg_cap, produced, early_exit, dense_out, grouped, a.hits, cnt, g, sup);
         }
         t = tn;
         cur = nxt;
@@ -173,7 +173,7 @@ __global__ __launch_bounds__(kTestWavesPerBlock * 64) void k_test_list(const Buc
         const uint32_t cn = c + n_waves;
         TileRef nxt = cur;
         if (cn < total) open_listed(descs, a.n_buckets, bi, cn, chunk_begin, count, j, t_log2, nxt);
-        produced = ts.run(cur, seg, a.seg_cap, produced, early_exit, dense_out, grouped, cnt);
+        produced = ts.run(cur, seg, a.seg_cap, produced, early_exit, dense_out, grouped, a.hits, cnt);
         c = cn;
         cur = nxt;
     }

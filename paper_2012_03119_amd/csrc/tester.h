@@ -450,13 +450,34 @@ struct Tester {
         }
     }
 
+    // The words of clause `id` that have a record, one bit each, into its entry: the
+    // lanes of a clause (up to 8 of them, a row of 8 lanes or part of one) join their
+    // four bits, and the first stores them.  A clause without records keeps its zero.
+    __device__ static void store_hits(void *hits, uint32_t id, uint32_t sub, const uint64_t (&af)[WPL],
+                                      const uint64_t (&ou)[WPL]) {
+        uint32_t m = 0;
+#pragma unroll
+        for (int i = 0; i < WPL; ++i) m |= (af[i] | ou[i]) ? 1u << i : 0u;
+        m <<= WPL * (sub & 7);
+        m |= __builtin_amdgcn_mov_dpp(m, 0xB1, 0xF, 0xF, true);                         // lane ^ 1
+        if constexpr (LPC >= 4) m |= __builtin_amdgcn_mov_dpp(m, 0x4E, 0xF, 0xF, true);  // lane ^ 2
+        if constexpr (LPC >= 8) m |= __builtin_amdgcn_mov_dpp(m, 0x141, 0xF, 0xF, true); // the other four of 8
+        if ((sub & 7) == 0 && m) {
+            if constexpr (LPC == 16) static_cast<uint32_t *>(hits)[2 * (uint64_t)id + sub / 8] = m;
+            else if constexpr (LPC == 8) static_cast<uint32_t *>(hits)[id] = m;
+            else if constexpr (LPC == 4) static_cast<uint16_t *>(hits)[id] = (uint16_t)m;
+            else static_cast<uint8_t *>(hits)[id] = (uint8_t)m;
+        }
+    }
+
     // Tests the clauses of an opened tile on chunk g of the rows.  Records go to
     // seg (capacity seg_cap) after the `produced` records already there; returns
     // the new count.  With dense != nullptr, writes each clause's mask row there
-    // instead.  grouped: a clause's records side by side.  sup: the clause's super-group mask (bit g clear: not tested).
+    // instead.  grouped: a clause's records side by side, and (hits) the
+    // words it has records in.  sup: the clause's super-group mask (bit g clear: not tested).
     // cnt (when cnt.on): what the wavefront did, added up.
     __device__ uint32_t run(const Tile &cur, gss_report *seg, uint32_t seg_cap, uint32_t produced, uint32_t early_exit,
-                            uint64_t *dense, bool grouped, Counts &cnt, uint32_t g = 0, uint64_t sup = ~0ull) const {
+                            uint64_t *dense, bool grouped, void *hits, Counts &cnt, uint32_t g = 0, uint64_t sup = ~0ull) const {
         // a low-priority clause sits out the runs where (run + id) % 4 != 0
         const bool skip = ((cur.lowword >> cur.lowshift) & 1u) && ((sched_run + cur.meta.y) & 3u) != 0;
         // chunk g: this lane's words g * RW + w0 .. (a clause whose super-group test
@@ -623,6 +644,9 @@ struct Tester {
             for (int i = 0; i < WPL; ++i) {
                 const uint64_t res = af[i] | ou[i];
                 if (res) recs[pos++] = u32x4{cur.meta.y, gw0 + i, (uint32_t)res, (uint32_t)(res >> 32)};
+            }
+            if constexpr (LPC > 1 && !WIDE) {
+                if (hits) store_hits(hits, cur.meta.y, lane % LPC, af, ou);
             }
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
