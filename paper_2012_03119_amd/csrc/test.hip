@@ -371,39 +371,39 @@ static bool begin_test(Ctx &c, uint32_t flags, Launch &L) {
 }
 
 // Completes a test begun by begin_test: waits, grows the report segments and
-// repeats the test once if they overflowed (unless GSS_TEST_NO_REGROW), and
-// publishes the counts.  Throws GSS_ERR_REPORT_OVERFLOW when records were lost.
+// repeats the test while they overflow (unless GSS_TEST_NO_REGROW), and publishes
+// the counts.  Mostly one repeat is enough; a scheduled test's list is in another
+// order each time, and so are the wavefronts' shares of the records.  Throws
+// GSS_ERR_REPORT_OVERFLOW when records were lost.
 static uint64_t end_test(Ctx &c, uint32_t flags, bool launched) {
     uint64_t n = 0, kept = 0;
     if (launched) {
         complete_with_overflow(c);
         n = c.h_summary[0];
         kept = c.h_summary[2];
-        const uint64_t largest = c.h_summary[1];
-        if (!(flags & GSS_TEST_DENSE) && largest > c.seg_cap && !(flags & GSS_TEST_NO_REGROW)) {
+        // every repeat has larger segments, and none needs more than all the records
+        for (uint64_t largest; !(flags & (GSS_TEST_DENSE | GSS_TEST_NO_REGROW)) && (largest = c.h_summary[1]) > c.seg_cap;) {
             const uint64_t want = largest + largest / 8 + kMinSegment;
-            bool grown = false;
             try {
                 gss_report *p = (gss_report *)c.dalloc((uint64_t)c.max_waves * want * sizeof(gss_report));
                 c.dfree(c.reports);
                 c.reports = p;
                 c.seg_cap = (uint32_t)want;
                 c.version++;
-                grown = true;
             } catch (const Error &e) {
                 if (e.code != GSS_ERR_CAPACITY) throw;
+                break;
             }
             // Repeating the test is only right while the state it saw is unchanged:
             // changes queued behind an asynchronous test would be in the rerun.
-            if (grown && c.mutations == c.launch_mutations) {
-                c.stats.regrows++;
-                Launch L = prepare(c, flags);
-                if (c.hits_armed) L.args.hits = c.hits;  // the same bits again
-                launch(c, L, flags, context_segments(c), true);
-                complete_with_overflow(c);
-                n = c.h_summary[0];
-                kept = c.h_summary[2];
-            }
+            if (c.mutations != c.launch_mutations) break;
+            c.stats.regrows++;
+            Launch L = prepare(c, flags);
+            if (c.hits_armed) L.args.hits = c.hits;  // the same bits again
+            launch(c, L, flags, context_segments(c), true);
+            complete_with_overflow(c);
+            n = c.h_summary[0];
+            kept = c.h_summary[2];
         }
     }
     c.stats.last_gathers = c.stats.last_gather_bytes = c.stats.last_agg_settled = 0;
