@@ -344,9 +344,9 @@ struct Tester {
 
     // Finishes the live clauses of the wavefront from literal k on (live: the lanes
     // with a live word); all lanes call it.  The lanes' own words wait in LDS
-    // meanwhile (each lane touches its own entries only): 76 registers in the plain
-    // kernel, 6 wavefronts per SIMD; it held 72 and 7 before, and forcing 7 with the
-    // spills that takes measured no faster.
+    // meanwhile (each lane touches its own entries only): 78 registers in the plain
+    // kernel, 6 wavefronts per SIMD; it held 72 and 7 without a join, and forcing 7 with
+    // the spills that takes measured no faster.
     __device__ void join(const Tile &cur, const char *pb, uint64_t live, uint32_t k, uint32_t len, uint64_t (&af)[WPL],
                          uint64_t (&ou)[WPL], uint32_t early_exit, Counts &cnt) const {
         const uint32_t lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
