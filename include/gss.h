@@ -209,8 +209,9 @@ gss_status gss_clear_slots(gss_ctx *ctx, uint32_t first_slot, uint32_t n_slots);
  * holds the exact count, and only the records that fit are kept (which ones is
  * unspecified).  Records come in a deterministic order for a given store, slot
  * set and device; with GSS_TEST_SORTED, gss_fetch_reports orders them by clause
- * id, then word (a device radix sort of every kept record at fetch time, which
- * needs 64 bytes of device memory per record; cap takes the first records of
+ * id, then word (on the device at fetch time, by ranking the marked (id, word)
+ * cells: at most 80 bytes of workspace per 64 cells; where that does not fit, by a
+ * radix sort, which needs 64 bytes per record; cap takes the first records of
  * that order).  GSS_TEST_SORTED with GSS_TEST_DENSE: INVALID_ARG. */
 gss_status gss_test(gss_ctx *ctx, uint32_t flags, uint64_t *out_n_reports);
 
