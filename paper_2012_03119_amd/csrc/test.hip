@@ -288,12 +288,16 @@ static void complete(Ctx &c) {
 }
 
 // The same, and after an overflow that the test kernel reported itself, the exact
-// counts of its segments from the finalize kernel.
+// counts of its segments from the finalize kernel.  That one runs behind whatever was
+// queued since the test, so the verdict it reads may be that of an update behind the
+// test: the test's own, which its kernel wrote, is put back.
 static void complete_with_overflow(Ctx &c) {
     complete(c);
     if (c.offsets_ready || !c.h_summary[1]) return;
+    const unsigned long long verdict = c.h_summary[3];
     queue_finalize(c, context_segments(c), c.last_waves, c.tests_launched);
     c.sync();
+    c.h_summary[3] = verdict;
     c.offsets_ready = true;
 }
 
