@@ -220,9 +220,10 @@ gss_status gss_test(gss_ctx *ctx, uint32_t flags, uint64_t *out_n_reports);
  * queued behind the test on the context's stream).  gss_test_query sets *done
  * once the results are in; gss_test_wait waits, then behaves as the end of
  * gss_test, with one difference: when the report segments overflowed and a call
- * changed the store, the planes or the active set after gss_test_async, the
- * segments are grown but the test is not repeated (a rerun would see the new
- * state): GSS_ERR_REPORT_OVERFLOW, with the exact count in *out_n_reports.  Only
+ * changed the store, the planes or the active set after gss_test_async, the test
+ * is not repeated (a rerun would see the new state): GSS_ERR_REPORT_OVERFLOW, with
+ * the exact count in *out_n_reports.  The records that fitted are kept, and the
+ * segments grow when the next test begins.  Only
  * one test may be in flight; gss_fetch_reports before gss_test_wait is
  * GSS_ERR_STATE. */
 gss_status gss_test_async(gss_ctx *ctx, uint32_t flags);
@@ -370,9 +371,9 @@ gss_status gss_batch_test(gss_batch *batch, uint32_t flags, uint64_t *out_n_repo
  * gss_batch_wait, the members count as having a test in flight (gss_test on them,
  * gss_fetch_reports and the like: GSS_ERR_STATE; gss_test_wait on a member: STATE,
  * naming gss_batch_wait).  gss_batch_wait returns what gss_batch_test would; a
- * store that overflowed is grown, and the batch repeated only when no member has
- * changed since the launch (else GSS_ERR_REPORT_OVERFLOW with exact counts, and
- * the next test fits). */
+ * batch with a store that overflowed is repeated, the store grown, only when no member
+ * has changed since the launch (else GSS_ERR_REPORT_OVERFLOW with exact counts; the
+ * records that fitted are kept, and the store grows with its next test). */
 gss_status gss_batch_test_async(gss_batch *batch, uint32_t flags);
 gss_status gss_batch_wait(gss_batch *batch, uint64_t *out_n_reports);
 

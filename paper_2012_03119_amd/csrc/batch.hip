@@ -346,12 +346,27 @@ bool same_schedule(const gss_schedule &x, const gss_schedule &y) {
     return x.order == y.order && x.chunk_tiles == y.chunk_tiles && x.blocks_per_cu == y.blocks_per_cu;
 }
 
+// Grows the report segments of the members whose last test overflowed; true when one grew.
+bool grow_members(gss_batch &b) {
+    bool grown = false;
+    for (Ctx *c : b.ctxs)
+        if (grow_segments(*c)) {
+            c->stats.regrows++;
+            grown = true;
+        }
+    return grown;
+}
+
 // Queues one batched test: plans (unless a valid graph is replayed) and
 // launches.  Every member counts it as a test of its own: its serial releases
 // the upload slots and deferred frees queued before it once it has completed.
 void launch_batch(gss_batch &b, uint32_t flags) {
     const uint32_t n = (uint32_t)b.ctxs.size();
     const bool use_graph = flags & GSS_TEST_GRAPH;
+    try {
+        grow_members(b);  // overflows that were not repeated at once
+    } catch (const Error &) {  // this test finds out whether it needs them
+    }
     const bool moved = refresh_aggregates(b, flags);
     bool valid = !moved && use_graph && b.graph_valid && b.graph_flags == flags && same_schedule(b.graph_sched, b.sched);
     for (uint32_t s = 0; valid && s < n; ++s) valid = b.versions[s] == b.ctxs[s]->version;
@@ -388,8 +403,9 @@ void launch_batch(gss_batch &b, uint32_t flags) {
 
 // Waits for the queued batched test (work queued after it may still run) and
 // publishes every store's counts into its context.  Returns true when some store
-// overflowed its report segments.
-bool complete_batch(gss_batch &b, uint32_t flags, bool &any_overflow_growable) {
+// overflowed its report segments: the records that fitted stay there, to be fetched,
+// until a repeat or the next test grows the segments.
+bool complete_batch(gss_batch &b, uint32_t flags) {
     const uint32_t n = (uint32_t)b.ctxs.size();
     GSS_HIP(hipEventSynchronize(b.ev1));
     float ms = 0.f;
@@ -398,7 +414,6 @@ bool complete_batch(gss_batch &b, uint32_t flags, bool &any_overflow_growable) {
     b.launches++;
 
     bool overflow = false;
-    any_overflow_growable = false;
     uint64_t act = 0;
     for (uint32_t s = 0; s < n; ++s) {
         Ctx &c = *b.ctxs[s];
@@ -422,20 +437,7 @@ bool complete_batch(gss_batch &b, uint32_t flags, bool &any_overflow_growable) {
         c.stats.last_literals = lits;
         if (sum[1] > c.seg_cap) {
             overflow = true;
-            if (!(flags & GSS_TEST_NO_REGROW)) {
-                const uint64_t want = sum[1] + sum[1] / 8 + kMinSegment;
-                try {
-                    gss_report *p = (gss_report *)c.dalloc((uint64_t)c.max_waves * want * sizeof(gss_report));
-                    c.dfree(c.reports);
-                    c.reports = p;
-                    c.seg_cap = (uint32_t)want;
-                    c.version++;
-                    c.stats.regrows++;
-                    any_overflow_growable = true;
-                } catch (const Error &e) {
-                    if (e.code != GSS_ERR_CAPACITY) throw;
-                }
-            }
+            if (!(flags & GSS_TEST_NO_REGROW)) c.seg_want = sum[1] + sum[1] / 8 + kMinSegment;
         }
     }
     // failed checks of queued updates: every context's verdict is cleared, the first reported
@@ -456,9 +458,9 @@ bool complete_batch(gss_batch &b, uint32_t flags, bool &any_overflow_growable) {
 }
 
 // One batched test, waited for.
-bool run_once(gss_batch &b, uint32_t flags, bool &any_overflow_growable) {
+bool run_once(gss_batch &b, uint32_t flags) {
     launch_batch(b, flags);
-    return complete_batch(b, flags, any_overflow_growable);
+    return complete_batch(b, flags);
 }
 
 void check_batch_flags(const gss_batch &b, uint32_t flags) {
@@ -549,9 +551,8 @@ extern "C" gss_status gss_batch_set_schedule(gss_batch *b, const gss_schedule *s
 extern "C" gss_status gss_batch_test(gss_batch *b, uint32_t flags, uint64_t *out_n_reports) {
     GSS_BATCH_BEGIN(b)
     check_batch_flags(*b_, flags);
-    bool grown = false;
-    bool overflow = run_once(*b_, flags, grown);
-    if (overflow && grown) overflow = run_once(*b_, flags, grown);
+    bool overflow = run_once(*b_, flags);
+    if (overflow && grow_members(*b_)) overflow = run_once(*b_, flags);
     const uint32_t n = (uint32_t)b_->ctxs.size();
     if (out_n_reports)
         for (uint32_t s = 0; s < n; ++s) out_n_reports[s] = b_->ctxs[s]->n_reports;
@@ -582,15 +583,14 @@ extern "C" gss_status gss_batch_wait(gss_batch *b, uint64_t *out_n_reports) {
     }
     const uint32_t flags = b_->pending_flags;
     const uint32_t n = (uint32_t)b_->ctxs.size();
-    bool grown = false;
     bool overflow = false;
     try {
-        overflow = complete_batch(*b_, flags, grown);
+        overflow = complete_batch(*b_, flags);
         // repeated at once only when no member has changed since the launch (a
         // change queued behind the test would be read by the repeat)
         bool unchanged = true;
         for (uint32_t s = 0; s < n; ++s) unchanged = unchanged && b_->ctxs[s]->mutations == b_->launch_mutations[s];
-        if (overflow && grown && unchanged) overflow = run_once(*b_, flags, grown);
+        if (overflow && unchanged && grow_members(*b_)) overflow = run_once(*b_, flags);
     } catch (...) {
         if (out_n_reports)
             for (uint32_t s = 0; s < n; ++s) out_n_reports[s] = b_->ctxs[s]->n_reports;
@@ -599,7 +599,7 @@ extern "C" gss_status gss_batch_wait(gss_batch *b, uint64_t *out_n_reports) {
     if (out_n_reports)
         for (uint32_t s = 0; s < n; ++s) out_n_reports[s] = b_->ctxs[s]->n_reports;
     GSS_REQUIRE(!overflow, GSS_ERR_REPORT_OVERFLOW,
-                "a store's report segments overflowed (now grown); its counts are exact: test again");
+                "a store's report segments overflowed (they grow with the next test); its counts are exact: test again");
     GSS_BATCH_END
 }
 

@@ -202,6 +202,7 @@ struct Ctx {
     gss_report *reports = nullptr;
     uint32_t max_waves = 0;                  // wavefronts of the largest test launch
     uint32_t seg_cap = 0;
+    uint64_t seg_want = 0;                   // records per segment that an overflow asked for (0: none did)
     uint32_t last_waves = 0;                 // wavefronts of the last launch
     uint32_t *seg_counts = nullptr;          // [max_waves]
     uint64_t *seg_offsets = nullptr;         // [max_waves + 1] exclusive prefix of the kept records
@@ -379,6 +380,9 @@ void copy_in(Ctx &c, void *dst, const void *src_hd, size_t bytes);
 // Queues the copy of the last test's first n kept records, as one list, into
 // device memory dst (on the context's stream).
 void queue_stitch(Ctx &c, gss_report *dst, uint64_t n);
+// Replaces the report segments by ones of seg_want records (the last test's records go);
+// false when nothing was wanted or there is no room.
+bool grow_segments(Ctx &c);
 hipError_t read_timing(Ctx &c) noexcept;  // the kernel time of a timed test into the statistics
 void scratch_setup(int device);  // once per device, from gss_create
 // Activity (learned priority enabled): state for ids below n_ids (validate

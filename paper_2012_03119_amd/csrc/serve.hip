@@ -618,7 +618,7 @@ void gss_server::run() {
         const uint64_t this_run = run_id - 1;
         res.runs++;
         if (overflow) {
-            // records were lost (the segments are grown now): the words are tested
+            // records were lost (the segments grow with the next run): the words are tested
             // again, with a newer snapshot where one is staged
             res.overflowed_runs++;
             if (log) std::fprintf(log, "X %llu %llu\n", (unsigned long long)this_run, (unsigned long long)n);

@@ -197,9 +197,8 @@ constexpr uint32_t kRankBlock = 1u << 16;  // cells per workgroup of the packing
 // words (rows under 8 words or over 64, the aggregate pre-test); one workgroup per segment.
 // A cell is a byte, stored, or (BITS) a bit, set by an atomic.  Bound by the segments'
 // reads (8 of each record's 16 bytes are used, but whole lines come in), or by the
-// atomics, carried out past the per-XCD caches at about 12 G a second.  Segments grown
-// after a test that lost records hold none yet: what is read there may be no cell,
-// and is left out (here and below).
+// atomics, carried out past the per-XCD caches at about 12 G a second.  No test writes a
+// record outside the table; one would be left out (here and below) rather than written.
 template <bool BITS>
 __global__ __launch_bounds__(256) void k_rank_mark(const gss_report *reports, const uint32_t *counts, uint32_t seg_cap,
                                                    uint32_t n_segments, uint32_t w_log2, uint32_t n_cells,

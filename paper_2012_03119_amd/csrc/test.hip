@@ -301,6 +301,24 @@ static void complete_with_overflow(Ctx &c) {
     c.offsets_ready = true;
 }
 
+bool grow_segments(Ctx &c) {
+    const uint64_t want = c.seg_want;
+    c.seg_want = 0;
+    if (want <= c.seg_cap) return false;
+    try {
+        gss_report *p = (gss_report *)c.dalloc((uint64_t)c.max_waves * want * sizeof(gss_report));
+        c.dfree(c.reports);
+        c.reports = p;
+        c.seg_cap = (uint32_t)want;
+        c.n_kept = 0;
+        c.version++;
+    } catch (const Error &e) {
+        if (e.code != GSS_ERR_CAPACITY) throw;
+        return false;
+    }
+    return true;
+}
+
 // Clears the hit words for a test whose records will be ordered, and gives them to its
 // kernel: the ordered fetch then has its marks without reading the records for them.
 // The words cost the test 1% and the records' marks took a third of the ordered fetch.
@@ -363,6 +381,10 @@ static bool begin_test(Ctx &c, uint32_t flags, Launch &L) {
     c.stats.last_pairs = c.live * act;
     c.stats.last_literals = lits;
     c.tested = false;
+    try {
+        grow_segments(c);  // an overflow that was not repeated at once
+    } catch (const Error &) {  // this test finds out whether it needs them
+    }
     L = prepare(c, flags);
     c.hits_armed = c.hits_valid = false;
     if (L.args.n_tiles == 0) {
@@ -387,20 +409,12 @@ static uint64_t end_test(Ctx &c, uint32_t flags, bool launched) {
         kept = c.h_summary[2];
         // every repeat has larger segments, and none needs more than all the records
         for (uint64_t largest; !(flags & (GSS_TEST_DENSE | GSS_TEST_NO_REGROW)) && (largest = c.h_summary[1]) > c.seg_cap;) {
-            const uint64_t want = largest + largest / 8 + kMinSegment;
-            try {
-                gss_report *p = (gss_report *)c.dalloc((uint64_t)c.max_waves * want * sizeof(gss_report));
-                c.dfree(c.reports);
-                c.reports = p;
-                c.seg_cap = (uint32_t)want;
-                c.version++;
-            } catch (const Error &e) {
-                if (e.code != GSS_ERR_CAPACITY) throw;
-                break;
-            }
+            c.seg_want = largest + largest / 8 + kMinSegment;
             // Repeating the test is only right while the state it saw is unchanged:
-            // changes queued behind an asynchronous test would be in the rerun.
-            if (c.mutations != c.launch_mutations) break;
+            // changes queued behind an asynchronous test would be in the rerun.  Without
+            // a repeat the records that fitted stay where they are, to be fetched, and
+            // the segments grow when the next test begins.
+            if (c.mutations != c.launch_mutations || !grow_segments(c)) break;
             c.stats.regrows++;
             Launch L = prepare(c, flags);
             if (c.hits_armed) L.args.hits = c.hits;  // the same bits again
