@@ -13,6 +13,7 @@
 
 #include "../../include/gss.h"
 #include "layout.h"
+#include "rank_plan.h"
 
 namespace gss {
 
@@ -398,12 +399,11 @@ bool rank_vars(Ctx &c);
 // Writes the n records at src (device) into dst (device) ordered by (clause id,
 // word); synchronises the stream.
 void sort_records(Ctx &c, gss_report *src, uint64_t n, gss_report *dst);  // src is overwritten
-// The same order straight from the report segments, by ranking (id, word) cells:
-// workspace bytes (0: use sort_records) and the queued launches.
-uint64_t rank_bytes(const Ctx &c);
-bool rank_uses_hits(uint64_t bytes);       // whether hit words of that size are ranked (and not too small or large)
-bool rank_is_small(const Ctx &c);  // one launch, which may write pinned host memory
-void rank_records(Ctx &c, char *ws, gss_report *dst, uint64_t limit);
+// The same order straight from the report segments, by ranking (id, word) cells: the
+// plan as things are (a small one is one launch, which may write pinned host memory)
+// and the queued launches.
+RankPlan rank_plan(const Ctx &c);
+void rank_records(Ctx &c, char *ws, uint64_t bytes, gss_report *dst, uint64_t limit);
 void launch_scan_u32(Ctx &c, uint32_t *x, uint64_t m);  // in place, exclusive, on c.stream
 uint32_t *deferred_flag(Ctx &c);
 uint32_t read_deferred(Ctx &c);

@@ -191,8 +191,6 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(const gss_report 
 
 // ---- ranked order ------------------------------------------------------------
 
-constexpr uint32_t kRankBlock = 1u << 16;  // cells per workgroup of the packing kernel (1024 words of 64)
-
 // Marks the cell id << w_log2 | word of every kept record, where the test kept no hit
 // words (rows under 8 words or over 64, the aggregate pre-test); one workgroup per segment.
 // A cell is a byte, stored, or (BITS) a bit, set by an atomic.  Bound by the segments'
@@ -335,8 +333,6 @@ __global__ __launch_bounds__(256) void k_rank_place(const gss_report *reports, c
 // The whole ranked order of a small result by one workgroup, its bit cells and counts
 // in LDS: one launch instead of five, 40 us of a 90 us pass of 20 K clauses x 64 slots.
 // 2^lanes_log2 lanes take a segment, about as many as it has records.
-constexpr uint32_t kSmallCells = 1u << 18, kSmallRecords = 1u << 14;
-
 __global__ __launch_bounds__(1024) void k_rank_small(const gss_report *reports, const uint32_t *counts, uint32_t seg_cap,
                                                      uint32_t n_segments, uint32_t lanes_log2, uint32_t w_log2,
                                                      uint32_t n_cells, uint64_t limit, gss_report *out) {
@@ -406,48 +402,8 @@ void launch_scan_u32(Ctx &c, uint32_t *x, uint64_t m) {
     GSS_HIP(hipGetLastError());
 }
 
-// The ranked order's plan for the last test's records: from the test's hit words where
-// it kept them (bit cells, already marked).  Otherwise bit cells cost an atomic a
-// record (2 M took 169 us), byte cells a byte written and one read a cell (96 M took
-// 45 us): bits where a record comes to 240 cells or more.  Then the cells cost little
-// (an eighth of a byte written and read) and so does the workspace, and the radix sort
-// (158 us for 43 K records, 238 us for 815 K) is left for cells beyond 2^31; the
-// kernels index cells by 32 bits.
-struct RankPlan {
-    uint32_t w_log2 = 0;
-    uint64_t cells = 0, words = 0, blocks = 0;
-    size_t marks = 0, packed = 0;  // bytes
-    bool hits = false, bits = false, fits = false, small = false;
-    explicit RankPlan(const Ctx &c) {
-        while ((1u << w_log2) < c.W) ++w_log2;  // a power of two of words per issued id
-        cells = ((uint64_t)c.id_loc.size() << w_log2) + 64;
-        words = (cells + 63) / 64;
-        blocks = (cells + kRankBlock - 1) / kRankBlock;
-        small = cells <= kSmallCells && c.n_kept <= kSmallRecords;
-        hits = c.hits_valid && !small;
-        if (hits) {  // the test's own bit cells
-            w_log2 = 0;
-            while ((1u << w_log2) < c.RWc) ++w_log2;
-            words = (c.hits_ids * c.RWc + 511) / 512 * 8;
-            cells = words * 64;
-            blocks = (cells + kRankBlock - 1) / kRankBlock;
-        }
-        bits = hits || c.n_kept < cells / 240;
-        marks = hits ? 0 : (words * (bits ? 8 : 64) + 255) / 256 * 256;
-        packed = (words * (bits ? 4 : 16) + 255) / 256 * 256;
-        fits = cells <= (1ull << 31);
-    }
-};
-
-bool rank_uses_hits(uint64_t bytes) { return bytes * 8 > kSmallCells && bytes * 8 <= (1ull << 31); }
-
-bool rank_is_small(const Ctx &c) { return RankPlan(c).small; }
-
-// Bytes of the ranked order's workspace, or 0 where the radix sort is used.
-uint64_t rank_bytes(const Ctx &c) {
-    const RankPlan p(c);
-    if (p.small) return 256;  // (none is used)
-    return p.fits ? p.marks + p.packed + (p.blocks * 4 + 255) / 256 * 256 : 0;
+RankPlan rank_plan(const Ctx &c) {
+    return RankPlan(c.id_loc.size(), c.W, c.RWc, c.n_kept, c.hits_valid, c.hits_ids);
 }
 
 template <bool BITS>
@@ -471,9 +427,10 @@ static void launch_rank(Ctx &c, const RankPlan &p, char *ws, gss_report *dst, ui
 }
 
 // Queues the ranked order of the last test's kept records, the first `limit` of it,
-// into dst (device); ws: rank_bytes of device memory, 256-byte aligned.
-void rank_records(Ctx &c, char *ws, gss_report *dst, uint64_t limit) {
-    const RankPlan p(c);
+// into dst (device); ws: `bytes` of device memory, 256-byte aligned, that the plan fits in.
+void rank_records(Ctx &c, char *ws, uint64_t bytes, gss_report *dst, uint64_t limit) {
+    const RankPlan p = rank_plan(c);
+    GSS_REQUIRE(p.fits_in(ws ? bytes : 0), GSS_ERR_DEVICE, "the ranked order does not fit its workspace");
     if (p.small) {
         uint32_t lanes_log2 = 0;
         while (lanes_log2 < 6 && ((uint64_t)c.last_waves << lanes_log2) < c.n_kept) ++lanes_log2;

@@ -477,40 +477,32 @@ void queue_stitch(Ctx &c, gss_report *dst, uint64_t n) {
 }
 
 // The first n of the ordered records into dst (device memory; the caller's when
-// dev).  Ranked from the segments when its workspace (`rank` bytes, at ws or
-// allocated here) is to be had; otherwise every kept record is stitched and
+// dev).  Ranked from the segments when its workspace (`bytes` at ws, or allocated
+// here) is to be had; otherwise every kept record is stitched and
 // radix-sorted, and the first n copied.  With 10.1 M records of 4 M clauses x 16 words
 // the ranked order's kernels take 0.13 ms from the test's hit words (place 115 us, pack
 // 5, clearing 3; without them mark 62, pack 15, place 111, clearing 12), where the
 // radix sort took 5.9 ms.
-static void fetch_sorted(Ctx &c, gss_report *dst, uint64_t n, bool dev, char *ws, uint64_t rank) {
-    if (rank) {
-        char *own = nullptr;
-        const bool small = rank_is_small(c);  // its cells are in LDS
-        if (rank_bytes(c) > rank) ws = nullptr;  // the hit words went to make room for ws
-        if (!ws && !small) {
-            try {
-                rank = rank_bytes(c);
-                ws = own = (char *)c.dalloc(rank);
-                if (rank_bytes(c) > rank) {
-                    c.dfree(own);
-                    ws = own = nullptr;
-                }
-            } catch (const Error &) {  // no room: the radix sort needs less where the cells outnumber the records
-            }
+static void fetch_sorted(Ctx &c, gss_report *dst, uint64_t n, bool dev, char *ws, uint64_t bytes) {
+    auto alloc = [&](uint64_t b) -> char * {
+        try {
+            return (char *)c.dalloc(b);
+        } catch (const Error &) {  // no room: the radix sort needs less where the cells outnumber the records
+            return nullptr;
         }
-        if (ws || small) {
-            try {
-                rank_records(c, ws, dst, n);
-                if (own) c.sync();
-            } catch (...) {
-                (void)hipStreamSynchronize(c.stream);
-                c.dfree(own);
-                throw;
-            }
-            c.dfree(own);
-            return;
+    };
+    const RankSpace s = rank_space([&] { return rank_plan(c); }, ws, bytes, alloc, [&](char *p) { c.dfree(p); });
+    if (s.ranked) {
+        try {
+            rank_records(c, s.ws, s.bytes, dst, n);
+            if (s.own) c.sync();
+        } catch (...) {
+            (void)hipStreamSynchronize(c.stream);
+            c.dfree(s.own);
+            throw;
         }
+        c.dfree(s.own);
+        return;
     }
     const uint64_t all = c.n_kept;
     gss_report *st = (gss_report *)c.dalloc(all * sizeof(gss_report));
@@ -614,10 +606,10 @@ extern "C" gss_status gss_fetch_reports(gss_ctx *ctx, gss_report *out, uint64_t 
         // A small list for the host is written straight into pinned memory by the
         // kernel that makes it and copied from there: a queued copy into the caller's
         // pageable memory took about 30 us.
-        if (!dev && n <= kDirectRecords && (!(c.last_flags & GSS_TEST_SORTED) || rank_is_small(c))) {
+        if (!dev && n <= kDirectRecords && (!(c.last_flags & GSS_TEST_SORTED) || rank_plan(c).small)) {
             gss_report *h = (gss_report *)c.host_stage(n * sizeof(gss_report));
             if (c.last_flags & GSS_TEST_SORTED)
-                rank_records(c, nullptr, (gss_report *)c.hdstage, n);
+                rank_records(c, nullptr, 0, (gss_report *)c.hdstage, n);
             else
                 queue_stitch(c, (gss_report *)c.hdstage, n);
             c.sync();
@@ -627,7 +619,8 @@ extern "C" gss_status gss_fetch_reports(gss_ctx *ctx, gss_report *out, uint64_t 
         }
         // host records pass through the bulk staging; a small ordered fetch has its
         // workspace behind them there
-        const uint64_t rank = (c.last_flags & GSS_TEST_SORTED) ? rank_bytes(c) : 0;
+        const RankPlan plan = rank_plan(c);
+        const uint64_t rank = (c.last_flags & GSS_TEST_SORTED) && plan.fits ? plan.bytes() : 0;
         const size_t head = dev ? 0 : (n * sizeof(gss_report) + 255) / 256 * 256;
         const bool staged = rank && head + rank <= std::max<size_t>(c.dstage_bytes, dev ? 0 : (size_t)1 << 20);
         char *stage = dev && !staged ? nullptr : (char *)c.device_stage(head + (staged ? rank : 0));
