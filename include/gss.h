@@ -27,6 +27,8 @@
  *    device values).  Unless a call says otherwise they are host memory.  Calls
  *    marked "host or device" also accept device pointers (detected with
  *    hipPointerGetAttributes); device inputs must stay valid until the call returns.
+ *    Device memory is read and written on the context's stream: what other streams
+ *    still do with it when the call is made is for the caller to order.
  *  - A context is not thread-safe: one thread drives it, like the single GPU
  *    manager thread of the paper's solver (Section 5).  Work is issued on the
  *    context's stream; calls that return results synchronise that stream.
@@ -318,6 +320,10 @@ gss_status gss_reset_stats(gss_ctx *ctx);
 
 /* hipStream_t the context issues work on (borrowed or owned). */
 gss_status gss_get_stream(const gss_ctx *ctx, void **stream);
+
+/* Device ordinal of device memory (as "host or device" arguments are told apart), -1 for
+ * host memory.  For callers that order a device output behind their own streams. */
+int32_t gss_pointer_device(const void *ptr);
 
 /* ---- Batched test: several independent stores in one persistent launch ----
  *

@@ -108,14 +108,16 @@ void report_deferred(Ctx &c, uint32_t verdict) {
                 "were not applied");
 }
 
-bool is_device_pointer(const void *p) {
+int pointer_device(const void *p) {
     hipPointerAttribute_t attr;
     if (hipPointerGetAttributes(&attr, p) != hipSuccess) {
         (void)hipGetLastError();  // plain pageable host memory
-        return false;
+        return -1;
     }
-    return attr.type == hipMemoryTypeDevice || attr.type == hipMemoryTypeManaged;
+    return attr.type == hipMemoryTypeDevice || attr.type == hipMemoryTypeManaged ? attr.device : -1;
 }
+
+bool is_device_pointer(const void *p) { return pointer_device(p) >= 0; }
 
 // ---------------------------------------------------------------------------
 // memory
@@ -494,3 +496,5 @@ extern "C" gss_status gss_get_stream(const gss_ctx *ctx, void **stream) {
     return GSS_OK;
 }
 
+
+extern "C" int32_t gss_pointer_device(const void *ptr) { return pointer_device(ptr); }

@@ -172,6 +172,7 @@ def load_library(path: Optional[str] = None):
         "gss_get_stats": ([P, ctypes.POINTER(gss_stats)], ctypes.c_int32),
         "gss_reset_stats": ([P], ctypes.c_int32),
         "gss_get_stream": ([P, ctypes.POINTER(P)], ctypes.c_int32),
+        "gss_pointer_device": ([P], ctypes.c_int32),
         "gss_update_words": ([P, u32, u32, P, P, P], ctypes.c_int32),
         "gss_update_vars": ([P, u32, u32, P, P, P], ctypes.c_int32),
         "gss_set_active": ([P, P], ctypes.c_int32),
@@ -392,23 +393,34 @@ def gss_fetch_reports(ctx, cap: int) -> np.ndarray:
     return out[:n.value]
 
 
-def _settle_outputs() -> None:
-    """Waits for torch's current stream before the context's stream writes a device
-    output.  The output's memory may be in use there still: torch hands a freed
-    tensor's memory out again at once, since it orders only its own stream, while
-    kernels queued on that stream have yet to read the old tensor."""
+def _order_behind_torch(ctx, *ptrs: int) -> None:
+    """Lets the context's stream wait for what torch's current stream has queued, on
+    the device that holds the memory at ptrs, before it writes an output there.  The
+    memory may be in use still: torch hands a freed tensor's memory out again at once,
+    since it orders only its own stream, while kernels queued on that stream have yet
+    to read the old tensor.  Host memory has nothing to wait for, and neither has a
+    call made while that stream is captured: what it holds runs with the graph."""
     torch = sys.modules.get("torch")
-    if torch is not None and torch.cuda.is_initialized():
-        cur = torch.cuda.current_stream()
-        if not cur.query():
-            cur.synchronize()
+    if torch is None or not torch.cuda.is_initialized():
+        return
+    lib = load_library()
+    for dev in {lib.gss_pointer_device(ctypes.c_void_p(p)) for p in ptrs}:
+        if dev < 0:
+            continue
+        cur = torch.cuda.current_stream(dev)
+        with torch.cuda.device(dev):
+            if torch.cuda.is_current_stream_capturing() or cur.query():
+                continue
+        own = gss_get_stream(ctx)
+        if own != cur.cuda_stream:
+            torch.cuda.ExternalStream(own, device=dev).wait_stream(cur)
 
 
 def gss_fetch_reports_into(ctx, ptr: int, cap: int) -> int:
     """Copies up to cap records into memory at address ptr (device or host, room
     for cap 16-byte records); returns how many were copied.  Device memory is
     written behind the work queued on torch's current stream."""
-    _settle_outputs()
+    _order_behind_torch(ctx, ptr)
     n = ctypes.c_uint64()
     _check(ctx, load_library().gss_fetch_reports(ctx, ctypes.c_void_p(ptr), cap, ctypes.byref(n)))
     return n.value
@@ -736,7 +748,7 @@ class Context:
         if not (out.is_cuda and out.is_contiguous()):
             raise ValueError("out must be a contiguous CUDA tensor")
         cap = out.numel() * out.element_size() // 16
-        _settle_outputs()
+        _order_behind_torch(self.ctx, out.data_ptr())
         n = gss_test_noalloc(self.ctx, flags, out.data_ptr(), cap)
         self._held = []
         return n

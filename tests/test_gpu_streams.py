@@ -28,3 +28,54 @@ def test_fetch_waits_for_the_callers_stream():
         got = buf.cpu().numpy().view(gss.REPORT_DTYPE).reshape(-1)
         want = ctx.fetch_reports(n)
         assert np.array_equal(got, want)
+
+
+def _small(ctx, w):
+    ctx.add_clauses(w.lits, w.offsets)
+    ctx.set_assignments(0, w.values)
+    n = ctx.test()
+    want = ctx.fetch_reports(n)  # (staging is allocated)
+    return n, want
+
+
+def test_host_output_does_not_wait_for_the_callers_stream():
+    """A fetch into host memory returns while torch's current stream still runs."""
+    import torch
+    w = gen.tiny(4)
+    with gss.Context(w.n_vars, 64) as ctx:
+        n, want = _small(ctx, w)
+        buf = np.empty(n, dtype=gss.REPORT_DTYPE)
+        work = torch.ones(1 << 28, dtype=torch.int32, device="cuda")
+        torch.cuda.synchronize()
+        for _ in range(800):  # about 200 ms
+            work.add_(1)
+        assert gss.gss_fetch_reports_into(ctx.ctx, buf.ctypes.data, n) == n
+        assert not torch.cuda.current_stream().query()
+        assert np.array_equal(buf, want)
+        torch.cuda.synchronize()
+
+
+def test_device_outputs_while_the_callers_stream_is_captured():
+    """Tests and fetches into device memory between the captured calls of another
+    stream: that stream cannot be waited for, and the capture goes on."""
+    import torch
+    w = gen.tiny(5)
+    with gss.Context(w.n_vars, 64) as ctx:
+        n, want = _small(ctx, w)
+        a = torch.full((n, 2), -7, dtype=torch.int64, device="cuda")
+        b = torch.full((n, 2), -7, dtype=torch.int64, device="cuda")
+        x = torch.zeros(1000, device="cuda")
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, capture_error_mode="relaxed"):
+            x.add_(1)
+            assert gss.gss_fetch_reports_into(ctx.ctx, a.data_ptr(), n) == n
+            assert ctx.test_noalloc(0, b) == n
+            x.add_(1)
+        for k in range(3):
+            g.replay()
+            torch.cuda.synchronize()
+            assert bool((x == 2 * (k + 1)).all())
+        for buf in (a, b):
+            assert np.array_equal(gss.sort_reports(buf.cpu().numpy().view(gss.REPORT_DTYPE).reshape(-1)),
+                                  gss.sort_reports(want))
