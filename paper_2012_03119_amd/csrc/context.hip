@@ -470,8 +470,8 @@ extern "C" const char *gss_last_error(const gss_ctx *ctx) {
 extern "C" gss_status gss_get_stats(const gss_ctx *ctx, gss_stats *out) {
     const Ctx *c = reinterpret_cast<const Ctx *>(ctx);
     if (!c || !out) return GSS_ERR_INVALID_ARG;
-    // the last test's events are read on demand
-    if (read_timing(*const_cast<Ctx *>(c)) != hipSuccess) return GSS_ERR_DEVICE;
+    // the last test's events are read on demand; the counters are returned whatever becomes of them
+    (void)read_timing(*const_cast<Ctx *>(c));
     *out = c->stats;
     out->live_clauses = c->live;
     out->device_bytes = c->device_bytes;

@@ -200,13 +200,24 @@ static Segments context_segments(Ctx &c) { return Segments{c.reports, c.seg_coun
 // Adds the kernel time of the last timed test to the statistics.  Its events are read
 // when the statistics are asked for, or before they are recorded again: reading them
 // as the test completes held the caller up for the second event, behind the kernel.
+// They are read in relaxed mode, since the caller may be capturing some other stream,
+// and left for later while it captures this one.
 hipError_t read_timing(Ctx &c) noexcept {
     if (!c.timing_pending) return hipSuccess;
-    c.timing_pending = false;
-    float ms = 0.f;
-    hipError_t e = hipEventSynchronize(c.ev_stop);
-    if (e == hipSuccess) e = hipEventElapsedTime(&ms, c.ev_start, c.ev_stop);
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    hipError_t e = hipThreadExchangeStreamCaptureMode(&mode);
     if (e != hipSuccess) return e;
+    float ms = 0.f;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    e = hipStreamIsCapturing(c.stream, &status);
+    const bool now = e == hipSuccess && status == hipStreamCaptureStatusNone;
+    if (now) {
+        c.timing_pending = false;
+        e = hipEventSynchronize(c.ev_stop);
+        if (e == hipSuccess) e = hipEventElapsedTime(&ms, c.ev_start, c.ev_stop);
+    }
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess || !now) return e;
     c.stats.last_kernel_ms = ms;
     c.stats.total_kernel_ms += ms;
     c.stats.timed_launches++;
@@ -230,8 +241,11 @@ static void launch(Ctx &c, Launch &L, uint32_t flags, const Segments &sg, bool s
     // dispatch instead, with hipExtLaunchKernel, measured slower: 24 against 10 us
     // of host time per launch, on the path between two tests)
     c.timed = serial % std::max<uint32_t>(1u, c.cfg.timing_interval) == 0;
-    if (c.timed) GSS_HIP(read_timing(c));
-    if (c.timed) GSS_HIP(hipEventRecord(c.ev_start, c.stream));
+    if (c.timed) {
+        GSS_HIP(read_timing(c));
+        c.timing_pending = false;
+        GSS_HIP(hipEventRecord(c.ev_start, c.stream));
+    }
     // records that will be ordered, or whose clauses' hits will be counted, come grouped
     const bool grouped = (flags & GSS_TEST_SORTED) || c.prio;
     summary = summary && L.grid < kMaxSummaryBlocks;

@@ -79,3 +79,50 @@ def test_device_outputs_while_the_callers_stream_is_captured():
         for buf in (a, b):
             assert np.array_equal(gss.sort_reports(buf.cpu().numpy().view(gss.REPORT_DTYPE).reshape(-1)),
                                   gss.sort_reports(want))
+
+
+@pytest.mark.parametrize("own", [True, False])
+def test_statistics_while_a_stream_is_captured(own):
+    """The last test's kernel time is read when the statistics are asked for: not
+    during a capture of the context's own stream, but after it; during a capture of
+    another stream without disturbing that."""
+    import torch
+    w = gen.tiny(6)
+    stream = torch.cuda.Stream()
+    with gss.Context(w.n_vars, 64, stream=stream) as ctx:
+        n, _ = _small(ctx, w)
+        x = torch.zeros(1000, device="cuda")
+        torch.cuda.synchronize()
+        ctx.reset_stats()
+        assert ctx.test() == n
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream if own else None, capture_error_mode="thread_local"):
+            x.add_(1)
+            assert ctx.stats()["last_reports"] == n
+        g.replay()
+        torch.cuda.synchronize()
+        assert bool((x == 1).all())
+        s = ctx.stats()
+        assert s["timed_launches"] == 1 and s["last_kernel_ms"] > 0
+
+
+def test_timed_tests_queued_while_another_stream_is_captured():
+    """A test queued during the capture of another stream, with the time of the test
+    before it not read yet."""
+    import torch
+    w = gen.tiny(7)
+    with gss.Context(w.n_vars, 64) as ctx:
+        n, _ = _small(ctx, w)
+        x = torch.zeros(1000, device="cuda")
+        torch.cuda.synchronize()
+        ctx.reset_stats()
+        assert ctx.test() == n
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, capture_error_mode="thread_local"):
+            x.add_(1)
+            ctx.test_async()
+        assert ctx.test_wait() == n
+        g.replay()
+        torch.cuda.synchronize()
+        assert bool((x == 1).all())
+        assert ctx.stats()["timed_launches"] == 2
