@@ -321,8 +321,8 @@ gss_status gss_reset_stats(gss_ctx *ctx);
 /* hipStream_t the context issues work on (borrowed or owned). */
 gss_status gss_get_stream(const gss_ctx *ctx, void **stream);
 
-/* Device ordinal of device memory (as "host or device" arguments are told apart), -1 for
- * host memory.  For callers that order a device output behind their own streams. */
+/* Device ordinal of device memory, -1 for host (or managed) memory.  For callers that
+ * order a device output behind their own streams. */
 int32_t gss_pointer_device(const void *ptr);
 
 /* ---- Batched test: several independent stores in one persistent launch ----

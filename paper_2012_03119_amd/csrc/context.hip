@@ -108,16 +108,27 @@ void report_deferred(Ctx &c, uint32_t verdict) {
                 "were not applied");
 }
 
-int pointer_device(const void *p) {
+bool is_device_pointer(const void *p) {
     hipPointerAttribute_t attr;
     if (hipPointerGetAttributes(&attr, p) != hipSuccess) {
         (void)hipGetLastError();  // plain pageable host memory
-        return -1;
+        return false;
     }
-    return attr.type == hipMemoryTypeDevice || attr.type == hipMemoryTypeManaged ? attr.device : -1;
+    return attr.type == hipMemoryTypeDevice || attr.type == hipMemoryTypeManaged;
 }
 
-bool is_device_pointer(const void *p) { return pointer_device(p) >= 0; }
+OutputPlace output_place(const void *p) {
+    OutputPlace o;
+    o.address = (uintptr_t)p;
+    hipPointerAttribute_t attr;
+    if (hipPointerGetAttributes(&attr, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return o;
+    }
+    o.device = attr.type == hipMemoryTypeDevice;
+    if (o.device) o.ordinal = attr.device;
+    return o;
+}
 
 // ---------------------------------------------------------------------------
 // memory
@@ -497,4 +508,4 @@ extern "C" gss_status gss_get_stream(const gss_ctx *ctx, void **stream) {
 }
 
 
-extern "C" int32_t gss_pointer_device(const void *ptr) { return pointer_device(ptr); }
+extern "C" int32_t gss_pointer_device(const void *ptr) { return output_place(ptr).ordinal; }

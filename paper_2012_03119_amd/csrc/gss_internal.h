@@ -13,6 +13,7 @@
 
 #include "../../include/gss.h"
 #include "layout.h"
+#include "outputs.h"
 #include "rank_plan.h"
 
 namespace gss {
@@ -371,7 +372,7 @@ void super_rebuild(Ctx &c, bool with_u);
 void launch_fill_u64(Ctx &c, uint64_t *p, uint64_t n, uint64_t value);
 void launch_fill_u32(Ctx &c, uint32_t *p, uint64_t n, uint32_t value);
 bool is_device_pointer(const void *p);
-int pointer_device(const void *p);  // device ordinal, -1 for host memory
+OutputPlace output_place(const void *p);
 unsigned fill_grid(uint64_t n);  // workgroups of 256 for a grid-stride pass over n items
 const uint32_t *queue_value_check(Ctx &c, const int8_t *values, uint64_t n);
 void queue_value_check_into(Ctx &c, const int8_t *values, uint64_t n, uint32_t *verdict);

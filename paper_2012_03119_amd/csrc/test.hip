@@ -669,10 +669,10 @@ extern "C" gss_status gss_fetch_masks(gss_ctx *ctx, const uint32_t *ids, uint32_
         }
     const size_t ids_bytes = ((size_t)n * 4 + 255) / 256 * 256;
     const size_t out_bytes = (size_t)n * c.W * 8;
-    const bool direct = is_device_pointer(out) && ((uintptr_t)out & 7) == 0;
+    const bool direct = stores_directly(output_place(out), c.device);
     // the list goes up through pinned memory (from a fresh vector, page by page and in
-    // pieces, 700 K ids took 0.3 ms); rows for the caller's device memory are gathered
-    // straight into it
+    // pieces, 700 K ids took 0.3 ms); rows for device memory of the caller's that the
+    // kernel may store to are gathered straight into it
     uint32_t *q = (uint32_t *)c.host_stage((size_t)n * 4);
     if (c.live == c.id_loc.size()) {  // no clause was ever removed
         std::memcpy(q, ids, (size_t)n * 4);
