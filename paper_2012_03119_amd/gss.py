@@ -434,6 +434,16 @@ def gss_fetch_masks(ctx, ids, n_words: int) -> np.ndarray:
     return out
 
 
+def gss_fetch_masks_into(ctx, ids, ptr: int) -> None:
+    """Copies the mask rows of ids into memory at address ptr (device or host, room
+    for uint64 [len(ids)][W]).  Device memory is written behind the work queued on
+    torch's current stream."""
+    ids = np.ascontiguousarray(ids, dtype=np.uint32)
+    if len(ids):
+        _order_behind_torch(ctx, ptr)
+        _check(ctx, load_library().gss_fetch_masks(ctx, _np_ptr(ids), len(ids), ctypes.c_void_p(ptr)))
+
+
 def gss_get_stats(ctx) -> dict:
     s = gss_stats()
     _check(ctx, load_library().gss_get_stats(ctx, ctypes.byref(s)))
@@ -513,6 +523,15 @@ def gss_mlp_forward(ctx, params, x) -> np.ndarray:
     out = np.zeros(n, dtype=np.float32)
     _check(ctx, load_library().gss_mlp_forward(ctx, _np_ptr(p), _np_ptr(x), n, _np_ptr(out)))
     return out
+
+
+def gss_mlp_forward_into(ctx, params, x: int, n: int, ptr: int) -> None:
+    """The same with the features (fp32 [n][12]) at address x and the probabilities
+    (fp32 [n]) written at address ptr, each device or host.  Device memory is used
+    behind the work queued on torch's current stream."""
+    p = _f32(params, (MLP_PARAMS,))
+    _order_behind_torch(ctx, x, ptr)
+    _check(ctx, load_library().gss_mlp_forward(ctx, _np_ptr(p), ctypes.c_void_p(x), n, ctypes.c_void_p(ptr)))
 
 
 def gss_mlp_loss_grad(ctx, params, x, y):

@@ -38,6 +38,41 @@ def _small(ctx, w):
     return n, want
 
 
+@pytest.mark.parametrize("call", ["masks", "forward"])
+def test_masks_and_forward_wait_for_the_callers_stream(call):
+    """The same for mask rows, and for the network, whose features also are still
+    being written when the call is made."""
+    import torch
+    w = gen.tiny(8)
+    rng = np.random.default_rng(8)
+    params = rng.standard_normal(gss.MLP_PARAMS).astype(np.float32) * 0.1
+    feats = rng.random((4096, 12), dtype=np.float32)
+    with gss.Context(w.n_vars, 64) as ctx:
+        ids = ctx.add_clauses(w.lits, w.offsets)
+        ctx.set_assignments(0, w.values)
+        ctx.test(gss.GSS_TEST_DENSE)
+        src = torch.from_numpy(feats).cuda()
+        x = torch.zeros_like(src)
+        if call == "masks":
+            want, buf = ctx.fetch_masks(ids), torch.full((len(ids), 1), -7, dtype=torch.int64, device="cuda")
+        else:
+            want, buf = gss.gss_mlp_forward(ctx.ctx, params, feats), torch.full((4096,), -7.0, device="cuda")
+        work = torch.ones(1 << 28, dtype=torch.int32, device="cuda")
+        torch.cuda.synchronize()
+        for _ in range(20):  # about 5 ms
+            work.add_(1)
+        x.copy_(src)
+        copy = buf.clone()
+        if call == "masks":
+            gss.gss_fetch_masks_into(ctx.ctx, ids, buf.data_ptr())
+            got = buf.cpu().numpy().view(np.uint64)
+        else:
+            gss.gss_mlp_forward_into(ctx.ctx, params, x.data_ptr(), 4096, buf.data_ptr())
+            got = buf.cpu().numpy()
+        assert bool((copy == -7).all())
+        assert np.array_equal(got, want)
+
+
 def test_host_output_does_not_wait_for_the_callers_stream():
     """A fetch into host memory returns while torch's current stream still runs."""
     import torch
