@@ -405,7 +405,9 @@ extern "C" gss_status gss_create(const gss_config *cfg, gss_ctx **out) {
         if (c->G == 1 && n_rows * c->RW * 8 >= (1ull << 32))
             throw Error(GSS_ERR_INVALID_ARG, "num_vars x max_slots too large: a plane table of at most 4096 slots "
                                              "must stay under 4 GiB");
-        // LDS staging: rows of variables 0..hot_vars, at most 64 KiB per workgroup (one chunk only)
+        // LDS staging: rows of variables 0..hot_vars, at most 64 KiB per workgroup (one chunk
+        // only): two workgroups fit a CU's 160 KiB, since the kernels of large tests keep
+        // less than 1 KiB beside the rows (those of small ones 16, see hot_joins)
         uint64_t max_rows = 65536 / (8ull * c->RWc);
         uint64_t rows = cfg->hot_vars && c->G == 1 ? 2ull * ((uint64_t)cfg->hot_vars + 1) : 0;
         if (rows > max_rows) rows = max_rows & ~1ull;

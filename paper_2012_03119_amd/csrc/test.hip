@@ -15,55 +15,70 @@ using KernelFn = void (*)(const BucketDesc *, const TestArgs, uint32_t, uint32_t
 
 // row words RW (power of two) -> lanes per clause and words per lane (a lane
 // takes one 32-byte sector: 4 words, or the whole row when it is shorter)
-template <int MODE, bool HOT, bool AGG>
+template <int MODE, bool HOT, bool AGG, bool JOIN = true>
 static KernelFn pick_rw(uint32_t rw) {
     switch (rw) {
-    case 1: return k_test<1, 1, MODE, HOT, AGG>;
-    case 2: return k_test<1, 2, MODE, HOT, AGG>;
-    case 4: return k_test<1, 4, MODE, HOT, AGG>;
-    case 8: return k_test<2, 4, MODE, HOT, AGG>;
-    case 16: return k_test<4, 4, MODE, HOT, AGG>;
-    case 32: return k_test<8, 4, MODE, HOT, AGG>;
-    default: return k_test<16, 4, MODE, HOT, AGG>;
+    case 1: return k_test<1, 1, MODE, HOT, AGG, false, JOIN>;
+    case 2: return k_test<1, 2, MODE, HOT, AGG, false, JOIN>;
+    case 4: return k_test<1, 4, MODE, HOT, AGG, false, JOIN>;
+    case 8: return k_test<2, 4, MODE, HOT, AGG, false, JOIN>;
+    case 16: return k_test<4, 4, MODE, HOT, AGG, false, JOIN>;
+    case 32: return k_test<8, 4, MODE, HOT, AGG, false, JOIN>;
+    default: return k_test<16, 4, MODE, HOT, AGG, false, JOIN>;
     }
 }
 
 template <bool AGG>
-static KernelFn pick_mode(uint32_t rw, int mode, bool hot) {
+static KernelFn pick_mode(uint32_t rw, int mode, bool hot, bool join) {
+    if constexpr (!AGG)
+        if (hot && !join) return mode == 0 ? pick_rw<0, true, false, false>(rw) : pick_rw<1, true, false, false>(rw);
     if (mode == 0) return hot ? pick_rw<0, true, AGG>(rw) : pick_rw<0, false, AGG>(rw);
     return hot ? pick_rw<1, true, AGG>(rw) : pick_rw<1, false, AGG>(rw);
 }
 
 // the scheduled test's kernel, which walks the list of the slots a run tests
-template <int MODE, bool HOT, bool AGG>
+template <int MODE, bool HOT, bool AGG, bool JOIN = true>
 static KernelFn pick_rw_list(uint32_t rw) {
     switch (rw) {
-    case 1: return k_test_list<1, 1, MODE, HOT, AGG>;
-    case 2: return k_test_list<1, 2, MODE, HOT, AGG>;
-    case 4: return k_test_list<1, 4, MODE, HOT, AGG>;
-    case 8: return k_test_list<2, 4, MODE, HOT, AGG>;
-    case 16: return k_test_list<4, 4, MODE, HOT, AGG>;
-    case 32: return k_test_list<8, 4, MODE, HOT, AGG>;
-    default: return k_test_list<16, 4, MODE, HOT, AGG>;
+    case 1: return k_test_list<1, 1, MODE, HOT, AGG, JOIN>;
+    case 2: return k_test_list<1, 2, MODE, HOT, AGG, JOIN>;
+    case 4: return k_test_list<1, 4, MODE, HOT, AGG, JOIN>;
+    case 8: return k_test_list<2, 4, MODE, HOT, AGG, JOIN>;
+    case 16: return k_test_list<4, 4, MODE, HOT, AGG, JOIN>;
+    case 32: return k_test_list<8, 4, MODE, HOT, AGG, JOIN>;
+    default: return k_test_list<16, 4, MODE, HOT, AGG, JOIN>;
     }
 }
 
 template <bool AGG>
-static KernelFn pick_mode_list(uint32_t rw, int mode, bool hot) {
+static KernelFn pick_mode_list(uint32_t rw, int mode, bool hot, bool join) {
+    if constexpr (!AGG)
+        if (hot && !join)
+            return mode == 0 ? pick_rw_list<0, true, false, false>(rw) : pick_rw_list<1, true, false, false>(rw);
     if (mode == 0) return hot ? pick_rw_list<0, true, AGG>(rw) : pick_rw_list<0, false, AGG>(rw);
     return hot ? pick_rw_list<1, true, AGG>(rw) : pick_rw_list<1, false, AGG>(rw);
 }
 
 // rw: words of a row in one chunk; wide: more than one chunk (no LDS staging then);
-// listed: a scheduled test that walks the list of the slots it tests
-static KernelFn pick_kernel(uint32_t rw, int mode, bool hot, bool agg, bool wide, bool listed = false) {
-    if (listed) return agg ? pick_mode_list<true>(rw, mode, hot) : pick_mode_list<false>(rw, mode, hot);
+// listed: a scheduled test that walks the list of the slots it tests; join: with
+// staging, whether long survivors are joined
+static KernelFn pick_kernel(uint32_t rw, int mode, bool hot, bool agg, bool wide, bool listed, bool join) {
+    if (listed) return agg ? pick_mode_list<true>(rw, mode, hot, join) : pick_mode_list<false>(rw, mode, hot, join);
     if (wide) {
         if (mode == 0) return agg ? k_test<16, 4, 0, false, true, true> : k_test<16, 4, 0, false, false, true>;
         return agg ? k_test<16, 4, 1, false, true, true> : k_test<16, 4, 1, false, false, true>;
     }
-    return agg ? pick_mode<true>(rw, mode, hot) : pick_mode<false>(rw, mode, hot);
+    return agg ? pick_mode<true>(rw, mode, hot, join) : pick_mode<false>(rw, mode, hot, join);
 }
+
+// Whether a test with staged rows joins its long survivors: up to two tiles per SIMD.  The
+// join keeps 16 KiB of LDS beside the rows and eight registers, which a test of many
+// tiles pays for with wavefronts; a small one leaves them idle, and lasts as long as
+// its longest chain.  Kernel us with and without the join, Zipf variables, one clause in
+// a hundred hit: 15 K clauses x 1024 slots 27 and 65, 30 K 61 and 72, 60 K (3750 tiles)
+// 78 and 83 (trigger mode 149 and 144), 1 M 217 and 191 (trigger 362 and 277; with 255
+// staged variables 372 and 260, 618 and 346); 120 K x 64 69 and 81, 250 K (3900 tiles) 92 and 80.
+static bool hot_joins(uint32_t tiles, int n_cu) { return tiles <= 8u * (uint32_t)n_cu; }
 
 struct Launch {
     TestArgs args{};
@@ -170,7 +185,8 @@ static Launch prepare(Ctx &c, uint32_t flags) {
         c.desc_shadow.assign(h, h + nb);
     }
     L.descs = (const BucketDesc *)c.d_desc;
-    L.fn = pick_kernel(c.RWc, (flags & GSS_TEST_TRIGGER) ? 1 : 0, hot, a.agg != nullptr, c.G > 1, listed);
+    L.fn = pick_kernel(c.RWc, (flags & GSS_TEST_TRIGGER) ? 1 : 0, hot, a.agg != nullptr, c.G > 1, listed,
+                       hot_joins(tiles, c.n_cu));
     if (hot) L.lds = (size_t)a.hot_rows * c.RW * 8;
     // persistent: exactly as many workgroups as fit on the device at once
     if (c.occ_fn != (const void *)L.fn || c.occ_lds != L.lds) {  // the query costs host time: cache it
@@ -337,11 +353,11 @@ bool grow_segments(Ctx &c) {
 // kernel: the ordered fetch then has its marks without reading the records for them.
 // The words cost the test 1% and the records' marks took a third of the ordered fetch.
 // Not where a clause's bits are less than a byte of its own, in rows of several chunks,
-// with the aggregate pre-test (few records, and not grouped), or for a table that
-// one workgroup orders; without the memory for them the fetch marks the records.
+// with the aggregate pre-test (few records, and not grouped), with staged rows, or for a
+// table that one workgroup orders; without the memory for them the fetch marks the records.
 static void arm_hits(Ctx &c, uint32_t flags, Launch &L) {
     c.hits_armed = c.hits_valid = false;
-    if (!(flags & GSS_TEST_SORTED) || L.args.agg || c.G > 1 || c.RWc < 8) return;
+    if (!(flags & GSS_TEST_SORTED) || L.args.agg || L.args.hot_rows || c.G > 1 || c.RWc < 8) return;
     const uint64_t bytes = (c.id_loc.size() * c.RWc / 8 + 63) / 64 * 64;
     if (!rank_uses_hits(bytes)) return;
     if (bytes > c.hits_bytes) {

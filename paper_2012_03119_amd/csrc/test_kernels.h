@@ -63,12 +63,13 @@ __device__ inline void finish_test(const TestArgs &a, uint32_t out, uint32_t pro
 
 // Each wavefront walks the tiles t = wave, wave + N, ... (N wavefronts in the
 // grid) and prefetches the next tile's metadata and first codes while it tests
-// the current one.  WIDE: plane rows of more than 64 words (several chunks).
-template <int LPC, int WPL, int MODE, bool HOT, bool AGG, bool WIDE = false>
+// the current one.  WIDE: plane rows of more than 64 words (several chunks).  JOIN:
+// long survivors are joined (with LDS staging there are kernels without, see hot_joins).
+template <int LPC, int WPL, int MODE, bool HOT, bool AGG, bool WIDE = false, bool JOIN = true>
 __global__ __launch_bounds__(kTestWavesPerBlock * 64) void k_test(const BucketDesc *__restrict__ descs,
                                                                    const TestArgs a, uint32_t early_exit,
                                                                    uint32_t out) {
-    using Ts = Tester<LPC, WPL, MODE, HOT, AGG, WIDE, join_rows<LPC, MODE, WIDE>>;
+    using Ts = Tester<LPC, WPL, MODE, HOT, AGG, WIDE, JOIN ? join_rows<LPC, MODE, WIDE> : 0>;
     extern __shared__ uint64_t lds_rows[];
     if constexpr (HOT) {
         const uint32_t n = a.hot_rows * Ts::RW;
@@ -129,11 +130,12 @@ __global__ __launch_bounds__(kTestWavesPerBlock * 64) void k_test(const BucketDe
 // Scheduled test: the wavefronts walk chunks of T listed slots (the clauses this
 // run tests, k_sched_list) instead of tiles, so that clauses sitting out the run
 // take no lanes.  Otherwise as k_test (no rows of more than 64 words).
-template <int LPC, int WPL, int MODE, bool HOT, bool AGG>
+template <int LPC, int WPL, int MODE, bool HOT, bool AGG, bool JOIN = true>
 __global__ __launch_bounds__(kTestWavesPerBlock * 64) void k_test_list(const BucketDesc *__restrict__ descs,
                                                                         const TestArgs a, uint32_t early_exit,
                                                                         uint32_t out) {
-    using Ts = Tester<LPC, WPL, MODE, HOT, AGG, false, HOT ? 1 : join_rows<LPC, MODE, false>>;  // HOT: 82 registers with two
+    using Ts = Tester<LPC, WPL, MODE, HOT, AGG, false,
+                      !JOIN ? 0 : HOT ? 1 : join_rows<LPC, MODE, false>>;  // HOT: 82 registers with two
     extern __shared__ uint64_t lds_rows[];
     __shared__ uint32_t chunk_begin[kMaxBuckets + 1], count[kMaxBuckets];
     if (threadIdx.x == 0) {

@@ -184,7 +184,7 @@ constexpr uint32_t join_rows = (MODE == 0 && LPC != 2 && !WIDE) ? 2 : 1;
 
 // One store's clause test for one lane: LPC lanes per clause, WPL words per lane,
 // a plane row of RW = LPC * WPL words.  MODE 0 = falsified, 1 = trigger.  ROWS:
-// steps of the join in flight together (join_rows).
+// steps of the join in flight together (join_rows; 0: no join).
 template <int LPC, int WPL, int MODE, bool HOT, bool AGG = false, bool WIDE = false, uint32_t ROWS = 1>
 struct Tester {
     static constexpr uint32_t kGroup = kGroupOf<AGG>;
@@ -506,7 +506,7 @@ struct Tester {
                 for (int i = 0; i < WPL; ++i) any |= af[i] | ou[i];
                 const uint64_t live = __ballot(lane_ok && k < len && (!early_exit || any != 0));
                 if (!live) break;
-                if constexpr (!AGG) {
+                if constexpr (!AGG && ROWS > 0) {
                     if (k >= kJoinFrom && joins(live, S - k)) {
                         join(cur, pb, live, k, len, af, ou, early_exit, cnt);
                         break;
@@ -630,6 +630,8 @@ struct Tester {
         // made use of, and not with the aggregate pre-test, where few tiles have records
         // and the registers cost a wavefront per SIMD (110 -> 122 us on 2 M clauses x
         // 2048 slots).
+        // With staged rows in the LDS the lanes store them themselves (and no hit words:
+        // four registers, a wavefront per SIMD, from 32 words on).
         uint32_t pos = 0, total = 0;
 #pragma unroll
         for (int i = 0; i < WPL; ++i) {
@@ -637,7 +639,20 @@ struct Tester {
             pos += lanes_below(bal);
             total += (uint32_t)__builtin_popcountll(bal);
         }
-        if (total) {  // uniform
+        if (!total) return produced;  // uniform
+        if constexpr (HOT) {
+#pragma unroll
+            for (int i = 0; i < WPL; ++i) {
+                const uint64_t res = af[i] | ou[i];
+                if (res) {
+                    if (produced + pos < seg_cap)
+                        reinterpret_cast<u32x4 *>(seg)[produced + pos] =
+                            u32x4{cur.meta.y, gw0 + i, (uint32_t)res, (uint32_t)(res >> 32)};
+                    ++pos;
+                }
+            }
+            produced += total;
+        } else {
             const uint32_t lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
             u32x4 *const recs = reinterpret_cast<u32x4 *>(park - lane);
 #pragma unroll
