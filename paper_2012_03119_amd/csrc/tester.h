@@ -322,10 +322,17 @@ struct Tester {
     //      x 1024 slots 737 and 535 us (trigger mode 1385 and 1102), 1 M x 320 trigger
     //      279 and 129, 700 K x 448 193 and 101, 20 K x 64 49 and 14.  Starting at 8
     //      read more than it saved (592 us at 4 M), at 16 it was no better (534).
+    //      In rows of several chunks a join starts at 16 in both modes: with that many
+    //      slots more clauses are live by chance at 12.  Falsified, without a join, from
+    //      12 and from 16: 500 K clauses x 16384 slots without hits 844, 915 and 865 us,
+    //      one clause in a thousand hit 1270, 962 and 967; 300 K x 4160 without hits 155,
+    //      185 and 166, one in a hundred hit 346, 254 and 254.  What is left of the loss
+    //      without hits is the registers (79 against 72, a wavefront per SIMD); 1 M x
+    //      16384 hierarchical slots, where the pre-test takes 101 us: 327, 370 and 369.
     //      With the aggregate pre-test a chain is a quarter as long (four rows in
     //      flight) and the registers cost a wavefront per SIMD (113 -> 131 us on
     //      2 M clauses x 2048 correlated slots): no joining there.
-    static constexpr uint32_t kJoinFrom = MODE == 0 ? 12 : 16;
+    static constexpr uint32_t kJoinFrom = MODE == 0 && !WIDE ? 12 : 16;
 
     // Joining n clauses takes about (rem / T + 2) steps each, the chain up to rem
     // (at least half of it: a length class spans a factor of two).
