@@ -322,6 +322,11 @@ struct Tester {
     //      x 1024 slots 737 and 535 us (trigger mode 1385 and 1102), 1 M x 320 trigger
     //      279 and 129, 700 K x 448 193 and 101, 20 K x 64 49 and 14.  Starting at 8
     //      read more than it saved (592 us at 4 M), at 16 it was no better (534).
+    //      What it costs: 8 batched stores without hits 820 -> 834 us, and where a chain is
+    //      short because its rows are in the L2 (Zipf variables, one clause in a hundred
+    //      hit) 500 K x 256 138 -> 159 us, trigger mode 170 -> 208, 1 M x 1024 185 -> 199.
+    //      Joining only where it saves more (a factor of 3 or 4 in joins()) brought these
+    //      to 149-153 and 189-193, but 1 M x 2048 from 255 to 278 and 332.
     //      In rows of several chunks a join starts at 16 in both modes: with that many
     //      slots more clauses are live by chance at 12.  Falsified, without a join, from
     //      12 and from 16: 500 K clauses x 16384 slots without hits 844, 915 and 865 us,
