@@ -214,7 +214,9 @@ gss_status gss_clear_slots(gss_ctx *ctx, uint32_t first_slot, uint32_t n_slots);
  * id, then word (on the device at fetch time, by ranking the marked (id, word)
  * cells: at most 80 bytes of workspace per 64 cells; where that does not fit, by a
  * radix sort, which needs 64 bytes per record; cap takes the first records of
- * that order).  GSS_TEST_SORTED with GSS_TEST_DENSE: INVALID_ARG. */
+ * that order).  An ordered test of rows of 8 to 64 words may also hold one bit per
+ * issued id and word of a row against hbm_budget_bytes; it is given up for any
+ * allocation that does not fit.  GSS_TEST_SORTED with GSS_TEST_DENSE: INVALID_ARG. */
 gss_status gss_test(gss_ctx *ctx, uint32_t flags, uint64_t *out_n_reports);
 
 /* The same test split in two: gss_test_async queues it and returns; the host may

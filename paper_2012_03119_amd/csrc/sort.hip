@@ -6,8 +6,9 @@
 // over the report segments marks the cells (a byte store each: no two records share
 // one, so no atomics; where the records are few among the cells, a bit each), one over
 // the cells takes the running counts of words of 64, and one more over the segments
-// stores each record at its place.  The records are read twice and written once,
-// straight from the segments.
+// stores each record at its place.  Where the test kept the marks itself (its hit words,
+// store_hits) the first pass is left out.  The records are read twice, or once with hit
+// words, and written once, straight from the segments.
 //
 // Radix (sort_records), where there are more than 2^31 cells or they do not fit the
 // memory budget: a least-significant-digit radix sort written for this library.  The key packs clause id and word ((id << word_bits) | word); each
